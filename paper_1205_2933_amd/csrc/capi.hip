@@ -214,6 +214,18 @@ __global__ void k_dc_canonical(const double2* __restrict__ in, double2* __restri
   out[i] = in[blk * n2 * n2 + (long long)col * n2 + row];
 }
 
+// y = D_c x in a reduced precision on canonical FP64 vectors: an FP32 copy of x
+// (a32) or its 16-bit packing (pack) first, so x and y may be one buffer
+void coarse_apply_reduced(mgdwf_handle h, const CoarseStore& s, mgdwf_prec prec, const double2* x, double2* y, int nrhs,
+                          float2* a32, char* pack) {
+  if (prec == MGDWF_F32) {
+    convert<double2, float2>(x, a32, h->coarse_len() * nrhs, h->st);
+    coarse_apply32(s, prec, a32, y, h->cg, nrhs, nullptr, h->g.ctile, h->st);
+  } else {
+    coarse_apply32(s, prec, x, y, h->cg, nrhs, pack, h->g.ctile, h->st);
+  }
+}
+
 }  // namespace
 
 extern "C" {
@@ -492,12 +504,9 @@ mgdwf_status mgdwf_apply_coarse(mgdwf_handle h, const double* in, double* out, i
     if (prec == MGDWF_F64) {
       coarse_apply64(s, reinterpret_cast<const double2*>(in), reinterpret_cast<double2*>(out), h->cg, nrhs, h->st);
     } else {
-      float2* a = h->buf<float2>("cio_a32", n);
-      float2* b = h->buf<float2>("cio_b32", n);
-      convert<double2, float2>(reinterpret_cast<const double2*>(in), a, n, h->st);
-      coarse_apply32(s, prec, a, b, h->cg, nrhs, h->buf<char>("cio_pack", coarse_pack_bytes(h->cg, nrhs)),
-                     h->g.ctile, h->st);
-      convert<float2, double2>(b, reinterpret_cast<double2*>(out), n, h->st);
+      coarse_apply_reduced(h, s, prec, reinterpret_cast<const double2*>(in), reinterpret_cast<double2*>(out), nrhs,
+                           prec == MGDWF_F32 ? h->buf<float2>("cio_a32", n) : nullptr,
+                           prec == MGDWF_F32 ? nullptr : h->buf<char>("cio_pack", coarse_pack_bytes(h->cg, nrhs)));
     }
   });
 }
@@ -532,10 +541,13 @@ mgdwf_status mgdwf_apply_coarse_noalloc(mgdwf_handle h, const double* in, double
     char* s = static_cast<char*>(h->scratch);
     float2* a = reinterpret_cast<float2*>(s);
     float2* b = reinterpret_cast<float2*>(s + vec);
-    convert<double2, float2>(x, a, n, h->st);
-    if (sq) sq_apply32(h->Asq.m32.as<float2>(), a, b, h->cg, nrhs, h->st);
-    else coarse_apply32(dagger ? h->DcH : h->Dc, prec, a, b, h->cg, nrhs, s + 2 * vec, h->g.ctile, h->st);
-    convert<float2, double2>(b, y, n, h->st);
+    if (sq) {
+      convert<double2, float2>(x, a, n, h->st);
+      sq_apply32(h->Asq.m32.as<float2>(), a, b, h->cg, nrhs, h->st);
+      convert<float2, double2>(b, y, n, h->st);
+    } else {
+      coarse_apply_reduced(h, dagger ? h->DcH : h->Dc, prec, x, y, nrhs, a, s + 2 * vec);
+    }
   });
 }
 

@@ -18,11 +18,13 @@
 // Dc[X][d] at ((X * 9 + d) * n2 + c) * n2 + r, so that lane r of a wavefront
 // reads consecutive addresses for a fixed column.
 #include <algorithm>
+#include <type_traits>
 
 #include <hip/hip_runtime.h>
 
 #include "mg_internal.h"
 #include "blas.h"
+#include "vecops.h"
 
 namespace mgdwf {
 
@@ -98,9 +100,9 @@ __global__ void k_adjoint_blocks(const double2* __restrict__ Dc, double2* __rest
 // block read once for all of them.  Workgroup = one coarse site, 9 wavefronts,
 // one per stencil direction d; lane = output row; the nine partial sums are
 // added in a fixed order through LDS.
-template <class MC2, class VC2, int NR>
+template <class MC2, class VC2, class O2, int NR>
 __global__ __launch_bounds__(576) void k_capply(const MC2* __restrict__ M, const VC2* __restrict__ x,
-                                                VC2* __restrict__ y, CoarseArgs a, int nrhs, int rhs0) {
+                                                O2* __restrict__ y, CoarseArgs a, int nrhs, int rhs0) {
   using T = typename real_of<VC2>::type;
   __shared__ T red[NR][64][2];
   const int X = blockIdx.x;
@@ -135,7 +137,7 @@ __global__ __launch_bounds__(576) void k_capply(const MC2* __restrict__ M, const
   }
   for (int i = threadIdx.x; i < nr * n2; i += blockDim.x) {
     const int j = i / n2, r = i % n2;
-    y[(long long)(rhs0 + j) * vs + (long long)X * n2 + r] = cmk<VC2>(red[j][r][0], red[j][r][1]);
+    y[(long long)(rhs0 + j) * vs + (long long)X * n2 + r] = cmk<O2>(red[j][r][0], red[j][r][1]);
   }
 }
 
@@ -189,13 +191,17 @@ __global__ __launch_bounds__(256) void k_pack_blocks(const double2* __restrict__
 // Coarse vectors -> 16-bit with one scale per (site, RHS):
 // xp[(rhs * Vc + X) * 2 n2 + k] = Re x_k / s, [.. + n2 + k] = Im x_k / s.
 // One wavefront per (RHS, site), lane k < n2 <= 64 handles component k.
-template <bool BF>
-__global__ __launch_bounds__(256) void k_pack_vec(const float2* __restrict__ x, uint16_t* __restrict__ xp,
+template <bool BF, class I2>
+__global__ __launch_bounds__(256) void k_pack_vec(const I2* __restrict__ x, uint16_t* __restrict__ xp,
                                                   float* __restrict__ xs, int Vc, int n2, int nrhs) {
   const long long i = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
   const int k = threadIdx.x & 63;
   if (i >= (long long)nrhs * Vc) return;  // whole wavefronts leave together
-  const float2 v = k < n2 ? x[i * n2 + k] : make_float2(0.f, 0.f);
+  float2 v = make_float2(0.f, 0.f);
+  if (k < n2) {
+    const I2 q = x[i * n2 + k];
+    v = make_float2((float)q.x, (float)q.y);
+  }
   float mx = fmaxf(fabsf(v.x), fabsf(v.y));
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
@@ -210,178 +216,333 @@ __global__ __launch_bounds__(256) void k_pack_vec(const float2* __restrict__ x, 
 
 typedef _Float16 h4v __attribute__((ext_vector_type(4)));
 typedef short s4v __attribute__((ext_vector_type(4)));
+typedef _Float16 h8v __attribute__((ext_vector_type(8)));
+typedef __bf16 b8v __attribute__((ext_vector_type(8)));
 typedef float f4v __attribute__((ext_vector_type(4)));
 
+// One MFMA on 16x16x16 (uint2: four k per lane) or gfx950's 16x16x32 tiles
+// (uint4: eight k per lane), FP16 or BF16 inputs, FP32 accumulation.
+// Whatever order the hardware gives the k-slots, A's and B's slot (lane group,
+// element) hold the same k, so the tile sum is the full contraction.
 template <bool BF>
 __device__ __forceinline__ f4v mfma16(uint2 a, uint2 b, f4v c) {
   if (BF) return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s4v, a), __builtin_bit_cast(s4v, b), c, 0, 0, 0);
   else return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(h4v, a), __builtin_bit_cast(h4v, b), c, 0, 0, 0);
 }
-
-// 16-bit coarse apply on MFMA, FP32 accumulation.  The complex product is the
-// real product of [[Re, -Im], [Im, Re]] (2 n2 x 2 n2) with [Re x; Im x]
-// (2 n2 x 16 RHS).  16x16x16 tiles: lane l holds A[row l%16][k 4(l/16)..+3],
-// B[k 4(l/16)..+3][col l%16] and C[row 4(l/16)..+3][col l%16].  Each
-// direction's tile sum is rescaled by (block scale) x (input scale of its RHS)
-// before it joins the FP32 accumulator.  Workgroup = one coarse site and a
-// chunk of 16 RHS; one wavefront per stencil direction d, the nine partial
-// results added in LDS in a fixed order.
 template <bool BF>
-__global__ __launch_bounds__(576) void k_capply_mfma(const uint16_t* __restrict__ Are, const uint16_t* __restrict__ Aim,
-                                                     const float* __restrict__ Asc, const uint16_t* __restrict__ xp,
-                                                     const float* __restrict__ xs, float2* __restrict__ y, CoarseArgs a,
-                                                     int nrhs) {
-  constexpr int MTMAX = 8;  // 2 n2 / 16 <= 8
-  __shared__ float red[128][17];
-  const int X = blockIdx.x;
-  const int rhs0 = blockIdx.y * 16;
-  const int n2 = a.n2;
-  const int MT = 2 * n2 / 16;
-  const int d = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const int col = l & 15, kq = l >> 4;
-  const int rhs = rhs0 + col;
-  const bool valid = rhs < nrhs;
-  const int Y = coarse_neighbour(a, X, d);
-  const long long blk = (long long)X * 9 + d;
-  uint2 bf[MTMAX];
-  const uint16_t* xrow = xp + ((long long)(valid ? rhs : 0) * a.Vc + Y) * 2 * n2;
-#pragma unroll
-  for (int kt = 0; kt < MTMAX; ++kt)
-    bf[kt] = (kt < MT && valid) ? *reinterpret_cast<const uint2*>(xrow + kt * 16 + 4 * kq) : make_uint2(0u, 0u);
-  f4v t[MTMAX];
-#pragma unroll
-  for (int m = 0; m < MTMAX; ++m) t[m] = f4v{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int mt = 0; mt < MTMAX; ++mt) {
-    if (mt >= MT) continue;
-    const int i = mt * 16 + (l & 15);           // expanded row
-    const bool im_row = i >= n2;
-    const int rr = im_row ? i - n2 : i;
-#pragma unroll
-    for (int kt = 0; kt < MTMAX; ++kt) {
-      if (kt >= MT) continue;
-      const int k = kt * 16 + 4 * kq;             // expanded column of this lane's 4 values
-      const bool im_col = k >= n2;
-      const int kk = im_col ? k - n2 : k;
-      const uint16_t* src = (im_row != im_col) ? Aim : Are;
-      uint2 av = *reinterpret_cast<const uint2*>(src + blk * n2 * n2 + (long long)rr * n2 + kk);
-      if (!im_row && im_col) { av.x ^= 0x80008000u; av.y ^= 0x80008000u; }  // -Im in the upper right
-      t[mt] = mfma16<BF>(av, bf[kt], t[mt]);
-    }
-  }
-  const float s = Asc[blk] * (valid ? xs[(long long)rhs * a.Vc + Y] : 0.f);
-  for (int w = 0; w < 9; ++w) {
-    if (d == w) {
-#pragma unroll
-      for (int mt = 0; mt < MTMAX; ++mt)
-        if (mt < MT)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            float& r = red[mt * 16 + 4 * kq + j][col];
-            r = (w == 0 ? 0.f : r) + s * t[mt][j];
-          }
-    }
-    __syncthreads();
-  }
-  for (int i = threadIdx.x; i < 16 * n2; i += blockDim.x) {
-    const int r = i % n2, cl = i / n2;
-    if (rhs0 + cl < nrhs) y[((long long)(rhs0 + cl) * a.Vc + X) * n2 + r] = make_float2(red[r][cl], red[n2 + r][cl]);
-  }
-}
-
-typedef _Float16 h8v __attribute__((ext_vector_type(8)));
-typedef __bf16 b8v __attribute__((ext_vector_type(8)));
-
-template <bool BF>
-__device__ __forceinline__ f4v mfma32(uint4 a, uint4 b, f4v c) {
+__device__ __forceinline__ f4v mfma16(uint4 a, uint4 b, f4v c) {
   if (BF) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(b8v, a), __builtin_bit_cast(b8v, b), c, 0, 0, 0);
   else return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8v, a), __builtin_bit_cast(h8v, b), c, 0, 0, 0);
 }
+__device__ __forceinline__ uint2 negate16(uint2 v) { return make_uint2(v.x ^ 0x80008000u, v.y ^ 0x80008000u); }
+__device__ __forceinline__ uint4 negate16(uint4 v) {
+  return make_uint4(v.x ^ 0x80008000u, v.y ^ 0x80008000u, v.z ^ 0x80008000u, v.w ^ 0x80008000u);
+}
 
-// k_capply_mfma on the 16x16x32 tiles of gfx950: a lane holds eight
-// consecutive k of its A row and of its B column (16-byte loads), so each
-// direction takes half the MFMA instructions and half the loads.  Whatever
-// order the hardware gives the 32 k-slots, A's and B's slot (lane group,
-// element) hold the same k, so the tile sum is the full contraction.  Needs
-// 2 n2 divisible by 32 (n2 by 16, as for every 16-bit store).
-// y(X) for RHS rhs0 .. rhs0 + 15 into red[row][col] (row < 2 n2: Re rows, then
-// Im rows).  Called by all 576 threads of a workgroup; ends with a barrier.
-template <bool BF>
-__device__ __forceinline__ void apply_site32(const uint16_t* Are, const uint16_t* Aim, const float* Asc,
-                                             const uint16_t* xp, const float* xs, const CoarseArgs& a, int nrhs,
-                                             int X, int rhs0, float (*red)[17]) {
-  // opaque to the optimiser, so a caller that applies in a loop recomputes
-  // the operator addresses each time instead of holding them in registers
-  int n2 = a.n2;
-  asm volatile("" : "+s"(X), "+s"(n2));
-  constexpr int MTMAX = 8;  // 2 n2 / 16 <= 8
-  constexpr int KTMAX = 4;  // 2 n2 / 32 <= 4
-  const int MT = 2 * n2 / 16, KT = 2 * n2 / 32;
-  const int d = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const int col = l & 15, kq = l >> 4;
-  const int rhs = rhs0 + col;
-  const bool valid = rhs < nrhs;
-  const int Y = coarse_neighbour(a, X, d);
-  const long long blk = (long long)X * 9 + d;
-  uint4 bf[KTMAX];
-  const uint16_t* xrow = xp + ((long long)(valid ? rhs : 0) * a.Vc + Y) * 2 * n2;
+// ---- the product at one coarse site, up to 16 right-hand sides, on MFMA
+//
+// y(X) = sum_d M[X][d] x(X + delta_d).  A workgroup of nine wavefronts owns the
+// site, wavefront d the direction d; the tile columns are the right-hand sides.
+// The rows of [Re M, Im M] (N2 x 2 N2) are loaded once and multiplied with
+// [Re x; -Im x] for Re y and with [Im x; Re x] for Im y.  Bound by the latency
+// of one round of loads (few sites) or by the bytes of M (many): N2 is a
+// template argument, so every load of the round is issued before the first
+// product waits for one.  With N2 at run time each tile's load waited for the
+// one before it: at 48 dof 12.6 us on 32 sites and 25.8 us on 512, one
+// right-hand side, against MNEW here.
+// Each wavefront leaves its tiles in its slab of LDS ([col][row], Re rows then
+// Im rows); slab_sum adds the nine in a fixed order.
+template <int N2> __host__ __device__ constexpr int slab_stride() { return 2 * N2 + 4; }
+template <int N2> __host__ __device__ constexpr int slab_floats() { return 9 * 16 * slab_stride<N2>(); }
+
+template <int N2>
+__device__ __forceinline__ float2 slab_sum(const float* slab, int col, int row) {
+  float2 s = make_float2(0.f, 0.f);
 #pragma unroll
-  for (int kt = 0; kt < KTMAX; ++kt)
-    bf[kt] = (kt < KT && valid) ? *reinterpret_cast<const uint4*>(xrow + kt * 32 + 8 * kq) : make_uint4(0u, 0u, 0u, 0u);
-  f4v t[MTMAX];
-#pragma unroll
-  for (int m = 0; m < MTMAX; ++m) t[m] = f4v{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int mt = 0; mt < MTMAX; ++mt) {
-    if (mt >= MT) continue;
-    const int i = mt * 16 + (l & 15);           // expanded row
-    const bool im_row = i >= n2;
-    const int rr = im_row ? i - n2 : i;
-#pragma unroll
-    for (int kt = 0; kt < KTMAX; ++kt) {
-      if (kt >= KT) continue;
-      const int k = kt * 32 + 8 * kq;             // expanded column of this lane's 8 values
-      const bool im_col = k >= n2;                // n2 % 8 == 0: the 8 stay on one side
-      const int kk = im_col ? k - n2 : k;
-      const uint16_t* src = (im_row != im_col) ? Aim : Are;
-      uint4 av = *reinterpret_cast<const uint4*>(src + blk * n2 * n2 + (long long)rr * n2 + kk);
-      if (!im_row && im_col) {  // -Im in the upper right
-        av.x ^= 0x80008000u; av.y ^= 0x80008000u; av.z ^= 0x80008000u; av.w ^= 0x80008000u;
-      }
-      t[mt] = mfma32<BF>(av, bf[kt], t[mt]);
-    }
+  for (int d = 0; d < 9; ++d) {
+    const float* q = slab + (d * 16 + col) * slab_stride<N2>() + row;
+    s.x += q[0];
+    s.y += q[N2];
   }
-  const float s = Asc[blk] * (valid ? xs[(long long)rhs * a.Vc + Y] : 0.f);
-  for (int w = 0; w < 9; ++w) {
-    if (d == w) {
+  return s;
+}
+
+template <int N2>
+__device__ __forceinline__ void slab_write(float* slab, const f4v* re, const f4v* im, float s) {
+  const int d = threadIdx.x >> 6, col = threadIdx.x & 15, kq = (threadIdx.x & 63) >> 4;
+  float* q = slab + (d * 16 + col) * slab_stride<N2>() + 4 * kq;
 #pragma unroll
-      for (int mt = 0; mt < MTMAX; ++mt)
-        if (mt < MT)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            float& r = red[mt * 16 + 4 * kq + j][col];
-            r = (w == 0 ? 0.f : r) + s * t[mt][j];
-          }
-    }
-    __syncthreads();
+  for (int mt = 0; mt < N2 / 16; ++mt) {
+    *reinterpret_cast<f4v*>(q + mt * 16) = s * re[mt];
+    *reinterpret_cast<f4v*>(q + N2 + mt * 16) = s * im[mt];
   }
 }
 
-template <bool BF>
-__global__ __launch_bounds__(576) void k_capply_mfma32(const uint16_t* __restrict__ Are,
-                                                       const uint16_t* __restrict__ Aim,
-                                                       const float* __restrict__ Asc, const uint16_t* __restrict__ xp,
-                                                       const float* __restrict__ xs, float2* __restrict__ y,
-                                                       CoarseArgs a, int nrhs) {
-  __shared__ float red[128][17];
-  const int X = blockIdx.x;
-  const int rhs0 = blockIdx.y * 16;
-  const int n2 = a.n2;
-  apply_site32<BF>(Are, Aim, Asc, xp, xs, a, nrhs, X, rhs0, red);
-  for (int i = threadIdx.x; i < 16 * n2; i += blockDim.x) {
-    const int r = i % n2, cl = i / n2;
-    if (rhs0 + cl < nrhs) y[((long long)(rhs0 + cl) * a.Vc + X) * n2 + r] = make_float2(red[r][cl], red[n2 + r][cl]);
+// 16-bit store: 16x16x16 tiles (SHAPE 0) or 16x16x32 tiles (SHAPE 1).  Each
+// direction's sum is rescaled by (block scale) x (input scale of its RHS).
+template <bool BF, int N2, int SHAPE>
+struct Site16 {
+  static constexpr int KL = SHAPE == 1 ? 8 : 4;  // consecutive k per lane
+  static constexpr int MT = N2 / 16, KT = 2 * N2 / (4 * KL);
+  using V = typename std::conditional<SHAPE == 1, uint4, uint2>::type;
+  V av[MT][KT], b1[KT], b2[KT];
+  float sc;
+
+  // issue the site's loads (xp: packed [rhs][site][Re, Im], xs: its scales)
+  __device__ __forceinline__ void load(const uint16_t* Are, const uint16_t* Aim, const float* Asc, const uint16_t* xp,
+                                       const float* xs, const CoarseArgs& a, int nrhs, int X, int rhs0) {
+    const int d = threadIdx.x >> 6, l = threadIdx.x & 63, kq = l >> 4;
+    const int rhs = rhs0 + (l & 15);
+    const bool valid = rhs < nrhs;
+    const long long blk = (long long)X * 9 + d;
+    const long long base = blk * N2 * N2 + (long long)(l & 15) * N2;
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+      const int k = (kt * 4 + kq) * KL;
+      const uint16_t* src = (k >= N2 ? Aim - N2 : Are) + base + k;
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) av[mt][kt] = *reinterpret_cast<const V*>(src + mt * 16 * N2);
+    }
+    const int Y = coarse_neighbour(a, X, d);
+    const long long iv = (long long)(valid ? rhs : 0) * a.Vc + Y;
+    const uint16_t* xrow = xp + iv * 2 * N2;
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+      const int k = (kt * 4 + kq) * KL;
+      b1[kt] = *reinterpret_cast<const V*>(xrow + k);
+      b2[kt] = *reinterpret_cast<const V*>(xrow + (k >= N2 ? k - N2 : k + N2));
+    }
+    sc = Asc[blk] * (valid ? xs[iv] : 0.f);
   }
+  // the products into this wavefront's slab; no barrier.  The columns past
+  // the last right-hand side repeat its row 0 with scale 0.
+  __device__ __forceinline__ void multiply(float* slab) {
+    f4v re[MT], im[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) re[mt] = im[mt] = f4v{0.f, 0.f, 0.f, 0.f};
+    const int kq = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+      const V bm = (kt * 4 + kq) * KL >= N2 ? negate16(b1[kt]) : b1[kt];
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        re[mt] = mfma16<BF>(av[mt][kt], bm, re[mt]);
+        im[mt] = mfma16<BF>(av[mt][kt], b2[kt], im[mt]);
+      }
+    }
+    slab_write<N2>(slab, re, im, sc);
+  }
+};
+
+// FP32 store (column-major float2 blocks) on 16x16x4 FP32 tiles: exact FP32
+// products, FP32 accumulation.  The vectors are read as they are.
+template <int N2>
+struct Site32 {
+  static constexpr int MT = N2 / 16, KT = N2 / 4;
+  const float2* A;
+  const float2* xv;
+  bool valid;
+  __device__ __forceinline__ void load(const float2* M, const float2* x, const CoarseArgs& a, int nrhs, int X, int rhs0) {
+    const int d = threadIdx.x >> 6, l = threadIdx.x & 63, kq = l >> 4;
+    const int rhs = rhs0 + (l & 15);
+    valid = rhs < nrhs;
+    A = M + ((long long)X * 9 + d) * N2 * N2 + kq * N2 + (l & 15);
+    xv = x + ((long long)(valid ? rhs : 0) * a.Vc + coarse_neighbour(a, X, d)) * N2 + kq;
+  }
+  __device__ __forceinline__ void multiply(float* slab) {
+    f4v re[MT], im[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) re[mt] = im[mt] = f4v{0.f, 0.f, 0.f, 0.f};
+    constexpr int KC = KT < 6 ? KT : (KT % 6 == 0 ? 6 : 4);  // k-tiles in flight together
+#pragma unroll
+    for (int k0 = 0; k0 < KT; k0 += KC) {
+      float2 m[MT][KC], v[KC];
+#pragma unroll
+      for (int q = 0; q < KC; ++q) {
+        v[q] = xv[4 * (k0 + q)];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) m[mt][q] = A[4 * (k0 + q) * N2 + mt * 16];
+      }
+#pragma unroll
+      for (int q = 0; q < KC; ++q) {
+        const float xr = valid ? v[q].x : 0.f, xi = valid ? v[q].y : 0.f;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+          re[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(m[mt][q].x, xr, re[mt], 0, 0, 0);
+          im[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(m[mt][q].x, xi, im[mt], 0, 0, 0);
+          re[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(m[mt][q].y, -xi, re[mt], 0, 0, 0);
+          im[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(m[mt][q].y, xr, im[mt], 0, 0, 0);
+        }
+      }
+    }
+    slab_write<N2>(slab, re, im, 1.f);
+  }
+};
+
+// y = D_c x from a 16-bit store; y as FP32 or FP64 complex numbers
+template <bool BF, int N2, int SHAPE, class O2>
+__global__ __launch_bounds__(576) void k_capply16(const uint16_t* __restrict__ Are, const uint16_t* __restrict__ Aim,
+                                                  const float* __restrict__ Asc, const uint16_t* __restrict__ xp,
+                                                  const float* __restrict__ xs, O2* __restrict__ y, CoarseArgs a,
+                                                  int nrhs) {
+  __shared__ __align__(16) float slab[slab_floats<N2>()];
+  const int X = blockIdx.x, rhs0 = blockIdx.y * 16, w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  Site16<BF, N2, SHAPE> s;
+  s.load(Are, Aim, Asc, xp, xs, a, nrhs, X, rhs0);
+  s.multiply(slab);
+  __syncthreads();
+  for (int c = w; c < min(16, nrhs - rhs0); c += 9)
+    if (l < N2) {
+      const float2 v = slab_sum<N2>(slab, c, l);
+      y[((long long)(rhs0 + c) * a.Vc + X) * N2 + l] = cmk<O2>(v.x, v.y);
+    }
+}
+
+// y = D_c x from the FP32 store
+template <int N2, class O2>
+__global__ __launch_bounds__(576) void k_capply32(const float2* __restrict__ M, const float2* __restrict__ x,
+                                                  O2* __restrict__ y, CoarseArgs a, int nrhs) {
+  __shared__ __align__(16) float slab[slab_floats<N2>()];
+  const int X = blockIdx.x, rhs0 = blockIdx.y * 16, w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  Site32<N2> s;
+  s.load(M, x, a, nrhs, X, rhs0);
+  s.multiply(slab);
+  __syncthreads();
+  for (int c = w; c < min(16, nrhs - rhs0); c += 9)
+    if (l < N2) {
+      const float2 v = slab_sum<N2>(slab, c, l);
+      y[((long long)(rhs0 + c) * a.Vc + X) * N2 + l] = cmk<O2>(v.x, v.y);
+    }
+}
+
+// ---- coarse CGNE, two launches per iteration
+//
+// The r-step applies D_c to p and, at its own site, moves x and r; the p-step
+// applies D_c^+ to r and forms the new p.  A launch also needs one sum over all
+// sites per right-hand side (|p|^2 for the r-step, the new |r|^2 for the
+// p-step): every workgroup adds the per-site partials the launch before left,
+// in the same fixed order, while its matrix loads are in flight.  Eight
+// launches (two packings, two products, two updates, two sums) took 48 us per
+// iteration on 32 sites with 12 right-hand sides and 81 us on 512 with one;
+// the two take 17 and 24 us.
+// Every workgroup reads all partials of its right-hand sides, so their traffic
+// grows as sites^2: at kPartMax (8192 partials, 64 KB per workgroup) it equals
+// the 16-bit matrix's own (83 KB per site at 48 dof, read from the same
+// caches); above, k_finalize_rhs (4 to 6 us) adds them first (np = 1, pstride =
+// NSLOT).
+struct CgneStep {
+  const double* part_in;  // right-hand side r: np partials at part_in + r * pstride
+  int np, pstride;
+  double* part_out;       // per (rhs, site), stride Vc
+  double* sl;             // slot table: |r|^2 of the current r at cur
+  int cur, nxt, aux;      // p-step: the sum goes to nxt (and to aux when >= 0)
+  int first;              // r-step: x = alpha p; p-step: p = t
+  float2 *x, *r, *p;
+  uint16_t *rp, *pp;      // packed r and p (16-bit stores only)
+  float *rs, *ps;
+};
+
+__device__ __forceinline__ double part_sum(const CgneStep& q, int rhs) {
+  const double* s = q.part_in + (long long)rhs * q.pstride;
+  double v = 0.0;
+#pragma unroll 8
+  for (int i = threadIdx.x & 63; i < q.np; i += 64) v += s[i];
+  return wave_sum(v);
+}
+
+// one wavefront: v (lane k < N2) -> 16 bits with one scale, and |v|^2
+template <bool BF, int N2>
+__device__ __forceinline__ void pack_wave(float2 v, uint16_t* o, float* scale) {
+  const int l = threadIdx.x & 63;
+  float mx = fmaxf(fabsf(v.x), fabsf(v.y));
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+  const float inv = mx > 0.f ? 1.f / mx : 0.f;
+  if (l == 0) *scale = mx;
+  if (l < N2) {
+    o[l] = to16<BF>(v.x * inv);
+    o[N2 + l] = to16<BF>(v.y * inv);
+  }
+}
+
+// KIND 0: FP32 store, 1: FP16, 2: BF16.  STEP 0: r-step (M = D_c), 1: p-step (M = D_c^+).
+template <int KIND, int N2, int SHAPE, int STEP>
+__global__ __launch_bounds__(576, N2 <= 48 ? 5 : 3) void k_cgne_step(const void* __restrict__ M0, const uint16_t* __restrict__ Aim,
+                                                   const float* __restrict__ Asc, CgneStep q, CoarseArgs a, int nrhs) {
+  __shared__ __align__(16) float slab[slab_floats<N2>()];
+  const int X = blockIdx.x, rhs0 = blockIdx.y * 16, w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const int nr = min(16, nrhs - rhs0);
+  typename std::conditional<KIND == 0, Site32<N2>, Site16<KIND == 2, N2, SHAPE>>::type s;
+  if constexpr (KIND == 0)
+    s.load(static_cast<const float2*>(M0), STEP == 0 ? q.p : q.r, a, nrhs, X, rhs0);
+  else
+    s.load(static_cast<const uint16_t*>(M0), Aim, Asc, STEP == 0 ? q.pp : q.rp, STEP == 0 ? q.ps : q.rs, a, nrhs, X, rhs0);
+  // this wavefront's right-hand sides, w and w + 9: their own entries and sums
+  float2 pv[2], xv[2], rv[2];
+  double sum[2] = {0.0, 0.0};
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int c = w + 9 * j;
+    pv[j] = xv[j] = rv[j] = make_float2(0.f, 0.f);
+    if (c < nr) {
+      if (l < N2) {
+        const long long i = ((long long)(rhs0 + c) * a.Vc + X) * N2 + l;
+        if (STEP == 0 || !q.first) pv[j] = q.p[i];
+        if (STEP == 0) {
+          rv[j] = q.r[i];
+          if (!q.first) xv[j] = q.x[i];
+        }
+      }
+      sum[j] = part_sum(q, rhs0 + c);
+    }
+  }
+  s.multiply(slab);
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int c = w + 9 * j;
+    if (c < nr) {
+      const int rhs = rhs0 + c;
+      const long long site = (long long)rhs * a.Vc + X, i = site * N2 + l;
+      const float2 t = l < N2 ? slab_sum<N2>(slab, c, l) : make_float2(0.f, 0.f);
+      double* sr = q.sl + (long long)rhs * NSLOT;
+      float2 v;
+      if (STEP == 0) {  // sum = |p|^2
+        const float alpha = (float)(sum[j] > 0.0 ? sr[q.cur] / sum[j] : 0.0);
+        v = make_float2(rv[j].x - alpha * t.x, rv[j].y - alpha * t.y);
+        if (l < N2) {
+          q.x[i] = make_float2(xv[j].x + alpha * pv[j].x, xv[j].y + alpha * pv[j].y);
+          q.r[i] = v;
+        }
+      } else {  // sum = the new |r|^2
+        const double rr = q.first ? 0.0 : sr[q.cur];
+        const float beta = (float)(rr > 0.0 ? sum[j] / rr : 0.0);
+        v = make_float2(t.x + beta * pv[j].x, t.y + beta * pv[j].y);
+        if (l < N2) q.p[i] = v;
+        if (X == 0 && l == 0) {
+          sr[q.nxt] = sum[j];
+          if (q.aux >= 0) sr[q.aux] = sum[j];
+        }
+      }
+      if constexpr (KIND != 0)
+        pack_wave<KIND == 2, N2>(v, (STEP == 0 ? q.rp : q.pp) + site * 2 * N2, (STEP == 0 ? q.rs : q.ps) + site);
+      const double nn = wave_sum((double)v.x * v.x + (double)v.y * v.y);
+      if (l == 0) q.part_out[site] = nn;
+    }
+  }
+}
+
+// r = b with its packing and per-site |r|^2; one wavefront per (rhs, site)
+template <int KIND, int N2>
+__global__ __launch_bounds__(256) void k_cgne_start(const float2* __restrict__ b, CgneStep q, long long nsites) {
+  const long long site = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int l = threadIdx.x & 63;
+  if (site >= nsites) return;  // whole wavefronts leave together
+  const float2 v = l < N2 ? b[site * N2 + l] : make_float2(0.f, 0.f);
+  if (l < N2) q.r[site * N2 + l] = v;
+  if constexpr (KIND != 0) pack_wave<KIND == 2, N2>(v, q.rp + site * 2 * N2, q.rs + site);
+  const double nn = wave_sum((double)v.x * v.x + (double)v.y * v.y);
+  if (l == 0) q.part_out[site] = nn;
 }
 
 // ---------------------------------------------------------------- persistent coarse CGNE
@@ -460,15 +621,26 @@ __device__ bool grid_barrier(GridSync* gs, unsigned nblocks, long long wait_tick
   return *ok_lds != 0;
 }
 
-template <bool BF>
+template <bool BF, int N2>
 __global__ __launch_bounds__(576) void k_cgne_persistent(PersistArgs q) {
-  __shared__ float red[128][17];
+  __shared__ __align__(16) float slab[slab_floats<N2>()];
   __shared__ float2 v[16][64];  // the current site's new r or p, per RHS
   __shared__ double rr0[16], rr[16], pp[16], rn[16];
   __shared__ int ok_lds;
   const CoarseArgs& a = q.a;
-  const int n2 = a.n2, nrhs = q.nrhs, Vc = a.Vc;
+  constexpr int n2 = N2;
+  const int nrhs = q.nrhs, Vc = a.Vc;
   const int G = gridDim.x;
+  // y(X) into the slabs; the site index is opaque to the optimiser, so the
+  // loop recomputes the operator addresses instead of holding them in registers
+  auto apply = [&](const uint16_t* Mre, const uint16_t* Mim, const float* Msc, const uint16_t* xp, const float* xs,
+                   int X) {
+    asm volatile("" : "+s"(X));
+    Site16<BF, N2, 1> s;
+    s.load(Mre, Mim, Msc, xp, xs, a, nrhs, X, 0);
+    s.multiply(slab);
+    __syncthreads();
+  };
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int ne = nrhs * n2;
   auto at = [&](int rhs, int X, int k) { return ((long long)rhs * Vc + X) * n2 + k; };
@@ -526,10 +698,10 @@ __global__ __launch_bounds__(576) void k_cgne_persistent(PersistArgs q) {
   if (threadIdx.x < nrhs) rr[threadIdx.x] = rr0[threadIdx.x];
   // p = D_c^+ r, |p|^2
   for (int X = blockIdx.x; X < Vc; X += G) {
-    apply_site32<BF>(q.Hre, q.Him, q.Hsc, q.rp, q.rs, a, nrhs, X, 0, red);
+    apply(q.Hre, q.Him, q.Hsc, q.rp, q.rs, X);
     for (int e = threadIdx.x; e < ne; e += blockDim.x) {
       const int rhs = e / n2, k = e - rhs * n2;
-      const float2 t = make_float2(red[k][rhs], red[n2 + k][rhs]);
+      const float2 t = slab_sum<N2>(slab, rhs, k);
       q.p[at(rhs, X, k)] = t;
       v[rhs][k] = t;
     }
@@ -542,13 +714,13 @@ __global__ __launch_bounds__(576) void k_cgne_persistent(PersistArgs q) {
   for (int it = 0; it < q.maxiter; ++it) {
     // q = D_c p; x += alpha p; r -= alpha q
     for (int X = blockIdx.x; X < Vc; X += G) {
-      apply_site32<BF>(q.Are, q.Aim, q.Asc, q.pp, q.ps, a, nrhs, X, 0, red);
+      apply(q.Are, q.Aim, q.Asc, q.pp, q.ps, X);
       for (int e = threadIdx.x; e < ne; e += blockDim.x) {
         const int rhs = e / n2, k = e - rhs * n2;
         const float alpha = (float)(pp[rhs] > 0.0 ? rr[rhs] / pp[rhs] : 0.0);
         const long long i = at(rhs, X, k);
         const float2 pv = q.p[i], xv = q.x[i], rv = q.r[i];
-        const float2 qv = make_float2(red[k][rhs], red[n2 + k][rhs]);
+        const float2 qv = slab_sum<N2>(slab, rhs, k);
         q.x[i] = make_float2(xv.x + alpha * pv.x, xv.y + alpha * pv.y);
         const float2 rn2 = make_float2(rv.x - alpha * qv.x, rv.y - alpha * qv.y);
         q.r[i] = rn2;
@@ -569,13 +741,14 @@ __global__ __launch_bounds__(576) void k_cgne_persistent(PersistArgs q) {
     if (done || n == q.maxiter) break;
     // t = D_c^+ r; p = t + beta p
     for (int X = blockIdx.x; X < Vc; X += G) {
-      apply_site32<BF>(q.Hre, q.Him, q.Hsc, q.rp, q.rs, a, nrhs, X, 0, red);
+      apply(q.Hre, q.Him, q.Hsc, q.rp, q.rs, X);
       for (int e = threadIdx.x; e < ne; e += blockDim.x) {
         const int rhs = e / n2, k = e - rhs * n2;
         const float beta = (float)(rr[rhs] > 0.0 ? rn[rhs] / rr[rhs] : 0.0);
         const long long i = at(rhs, X, k);
         const float2 pv = q.p[i];
-        const float2 t = make_float2(red[k][rhs] + beta * pv.x, red[n2 + k][rhs] + beta * pv.y);
+        const float2 s = slab_sum<N2>(slab, rhs, k);
+        const float2 t = make_float2(s.x + beta * pv.x, s.y + beta * pv.y);
         q.p[i] = t;
         v[rhs][k] = t;
       }
@@ -642,7 +815,7 @@ void coarse_apply64(const CoarseStore& s, const double2* x, double2* y, const Co
                     hipStream_t st) {
   if (cg.n2 > 64) fail(MGDWF_ERR_INVALID_ARG, "2*nvec above 64 is not supported");
   for (int r0 = 0; r0 < nrhs; r0 += 8) {
-    hipLaunchKernelGGL((k_capply<double2, double2, 8>), dim3(cg.Vc), dim3(576), 0, st, s.m64.as<double2>(), x, y,
+    hipLaunchKernelGGL((k_capply<double2, double2, double2, 8>), dim3(cg.Vc), dim3(576), 0, st, s.m64.as<double2>(), x, y,
                        coarse_args(cg), nrhs, r0);
     MG_LAUNCH_CHECK();
   }
@@ -652,14 +825,37 @@ size_t coarse_pack_bytes(const CoarseGeometry& cg, int nrhs) {
   return (size_t)nrhs * cg.Vc * (2 * cg.n2 * sizeof(uint16_t) + sizeof(float)) + 256;
 }
 
-void coarse_apply32(const CoarseStore& s, mgdwf_prec prec, const float2* x, float2* y, const CoarseGeometry& cg,
-                    int nrhs, void* pack, int ctile, hipStream_t st) {
+// f(N2) with the coarse dof count as a compile-time constant; false where the
+// MFMA kernels have none (2 Nv not a multiple of 16)
+template <class F>
+static bool with_n2(int n2, F&& f) {
+  switch (n2) {
+    case 16: f(std::integral_constant<int, 16>{}); return true;
+    case 32: f(std::integral_constant<int, 32>{}); return true;
+    case 48: f(std::integral_constant<int, 48>{}); return true;
+    case 64: f(std::integral_constant<int, 64>{}); return true;
+    default: return false;
+  }
+}
+
+template <class I2, class O2>
+void coarse_apply32(const CoarseStore& s, mgdwf_prec prec, const I2* x, O2* y, const CoarseGeometry& cg, int nrhs,
+                    void* pack, int ctile, hipStream_t st) {
   if (cg.n2 > 64) fail(MGDWF_ERR_INVALID_ARG, "2*nvec above 64 is not supported");
+  const CoarseArgs a = coarse_args(cg);
+  const dim3 grid(cg.Vc, ceil_div(nrhs, 16));
   if (prec == MGDWF_F32 || prec == MGDWF_F64) {
-    for (int r0 = 0; r0 < nrhs; r0 += 16) {
-      hipLaunchKernelGGL((k_capply<float2, float2, 16>), dim3(cg.Vc), dim3(576), 0, st, s.m32.as<float2>(), x, y,
-                         coarse_args(cg), nrhs, r0);
+    if constexpr (std::is_same<I2, float2>::value) {
+      if (!with_n2(cg.n2, [&](auto N) {
+            hipLaunchKernelGGL((k_capply32<decltype(N)::value, O2>), grid, dim3(576), 0, st, s.m32.as<float2>(), x, y, a,
+                               nrhs);
+          }))
+        for (int r0 = 0; r0 < nrhs; r0 += 16)  // other dof counts: one lane per row
+          hipLaunchKernelGGL((k_capply<float2, float2, O2, 16>), dim3(cg.Vc), dim3(576), 0, st, s.m32.as<float2>(), x,
+                             y, a, nrhs, r0);
       MG_LAUNCH_CHECK();
+    } else {
+      fail(MGDWF_ERR_INVALID_ARG, "the FP32 coarse operator takes FP32 vectors");
     }
     return;
   }
@@ -668,27 +864,147 @@ void coarse_apply32(const CoarseStore& s, mgdwf_prec prec, const float2* x, floa
   uint16_t* xp = static_cast<uint16_t*>(pack);
   float* xs = reinterpret_cast<float*>(xp + (size_t)nrhs * cg.Vc * 2 * cg.n2);
   const long long nsv = (long long)nrhs * cg.Vc;
-  if (bf) hipLaunchKernelGGL(k_pack_vec<true>, dim3(ceil_div(nsv, 4)), dim3(256), 0, st, x, xp, xs, cg.Vc, cg.n2, nrhs);
-  else hipLaunchKernelGGL(k_pack_vec<false>, dim3(ceil_div(nsv, 4)), dim3(256), 0, st, x, xp, xs, cg.Vc, cg.n2, nrhs);
-  MG_LAUNCH_CHECK();
-  dim3 grid(cg.Vc, ceil_div(nrhs, 16));
-  if (ctile == 1) {  // 16x16x32 tiles
-    if (bf)
-      hipLaunchKernelGGL(k_capply_mfma32<true>, grid, dim3(576), 0, st, s.reb.as<uint16_t>(), s.imb.as<uint16_t>(),
-                         s.scb.as<float>(), xp, xs, y, coarse_args(cg), nrhs);
-    else
-      hipLaunchKernelGGL(k_capply_mfma32<false>, grid, dim3(576), 0, st, s.re16.as<uint16_t>(),
-                         s.im16.as<uint16_t>(), s.sc16.as<float>(), xp, xs, y, coarse_args(cg), nrhs);
-    MG_LAUNCH_CHECK();
-    return;
-  }
   if (bf)
-    hipLaunchKernelGGL(k_capply_mfma<true>, grid, dim3(576), 0, st, s.reb.as<uint16_t>(), s.imb.as<uint16_t>(),
-                       s.scb.as<float>(), xp, xs, y, coarse_args(cg), nrhs);
+    hipLaunchKernelGGL((k_pack_vec<true, I2>), dim3(ceil_div(nsv, 4)), dim3(256), 0, st, x, xp, xs, cg.Vc, cg.n2, nrhs);
   else
-    hipLaunchKernelGGL(k_capply_mfma<false>, grid, dim3(576), 0, st, s.re16.as<uint16_t>(), s.im16.as<uint16_t>(),
-                       s.sc16.as<float>(), xp, xs, y, coarse_args(cg), nrhs);
+    hipLaunchKernelGGL((k_pack_vec<false, I2>), dim3(ceil_div(nsv, 4)), dim3(256), 0, st, x, xp, xs, cg.Vc, cg.n2, nrhs);
   MG_LAUNCH_CHECK();
+  const uint16_t* re = (bf ? s.reb : s.re16).as<uint16_t>();
+  const uint16_t* im = (bf ? s.imb : s.im16).as<uint16_t>();
+  const float* sc = (bf ? s.scb : s.sc16).as<float>();
+  with_n2(cg.n2, [&](auto N) {
+    constexpr int N2 = decltype(N)::value;
+#define MG_CA(BF, SH) hipLaunchKernelGGL((k_capply16<BF, N2, SH, O2>), grid, dim3(576), 0, st, re, im, sc, xp, xs, y, a, nrhs)
+    if (bf && ctile == 1) MG_CA(true, 1);
+    else if (bf) MG_CA(true, 0);
+    else if (ctile == 1) MG_CA(false, 1);
+    else MG_CA(false, 0);
+#undef MG_CA
+  });
+  MG_LAUNCH_CHECK();
+}
+template void coarse_apply32<float2, float2>(const CoarseStore&, mgdwf_prec, const float2*, float2*,
+                                             const CoarseGeometry&, int, void*, int, hipStream_t);
+template void coarse_apply32<float2, double2>(const CoarseStore&, mgdwf_prec, const float2*, double2*,
+                                              const CoarseGeometry&, int, void*, int, hipStream_t);
+template void coarse_apply32<double2, double2>(const CoarseStore&, mgdwf_prec, const double2*, double2*,
+                                               const CoarseGeometry&, int, void*, int, hipStream_t);
+
+// ---- coarse CGNE on the fused steps
+// Partials per launch up to which every workgroup adds them itself.
+constexpr long long kPartMax = 8192;
+
+bool cgne_fused(const CoarseGeometry& cg, mgdwf_prec prec) {
+  return (prec == MGDWF_F32 || prec == MGDWF_F16 || prec == MGDWF_BF16) && cg.n2 % 16 == 0 && cg.n2 <= 64;
+}
+
+size_t cgne_fused_bytes(const CoarseGeometry& cg, int nrhs) {
+  const size_t nsv = (size_t)nrhs * cg.Vc;
+  return 2 * nsv * 2 * cg.n2 * sizeof(uint16_t) + 2 * nsv * sizeof(float) + 2 * nsv * sizeof(double) + 6 * 256;
+}
+
+static CgneStep cgne_carve(void* work, const CoarseGeometry& cg, int nrhs, float2* x, float2* r, float2* p,
+                           double** part_r, double** part_p) {
+  const size_t nsv = (size_t)nrhs * cg.Vc;
+  char* w = static_cast<char*>(work);
+  auto take = [&](size_t bytes) {
+    char* q = w;
+    w += (bytes + 255) / 256 * 256;
+    return q;
+  };
+  CgneStep q{};
+  q.x = x;
+  q.r = r;
+  q.p = p;
+  q.rp = reinterpret_cast<uint16_t*>(take(nsv * 2 * cg.n2 * sizeof(uint16_t)));
+  q.pp = reinterpret_cast<uint16_t*>(take(nsv * 2 * cg.n2 * sizeof(uint16_t)));
+  q.rs = reinterpret_cast<float*>(take(nsv * sizeof(float)));
+  q.ps = reinterpret_cast<float*>(take(nsv * sizeof(float)));
+  *part_r = reinterpret_cast<double*>(take(nsv * sizeof(double)));
+  *part_p = reinterpret_cast<double*>(take(nsv * sizeof(double)));
+  q.aux = -1;
+  return q;
+}
+
+// partials of the launch before: added in the kernel, or first by k_finalize_rhs into slot `tmp`
+static void cgne_partials(CgneStep& q, const double* part, const CoarseGeometry& cg, int nrhs, double* sl, int tmp,
+                          hipStream_t st) {
+  q.sl = sl;
+  if ((long long)std::min(nrhs, 16) * cg.Vc <= kPartMax) {
+    q.part_in = part;
+    q.np = q.pstride = cg.Vc;
+  } else {
+    finalize_rhs(part, cg.Vc, 1, sl, tmp, nrhs, st);
+    q.part_in = sl + tmp;
+    q.np = 1;
+    q.pstride = NSLOT;
+  }
+}
+
+template <int STEP>
+static void cgne_launch(const CoarseStore& s, mgdwf_prec prec, int ctile, const CgneStep& q, const CoarseGeometry& cg,
+                        int nrhs, hipStream_t st) {
+  const dim3 grid(cg.Vc, ceil_div(nrhs, 16));
+  const CoarseArgs a = coarse_args(cg);
+  const bool bf = prec == MGDWF_BF16;
+  const uint16_t* im = (bf ? s.imb : s.im16).as<uint16_t>();
+  const float* sc = (bf ? s.scb : s.sc16).as<float>();
+  with_n2(cg.n2, [&](auto N) {
+    constexpr int N2 = decltype(N)::value;
+#define MG_CS(K, SH, M) hipLaunchKernelGGL((k_cgne_step<K, N2, SH, STEP>), grid, dim3(576), 0, st, M, im, sc, q, a, nrhs)
+    if (prec == MGDWF_F32) MG_CS(0, 0, s.m32.p);
+    else if (bf && ctile == 1) MG_CS(2, 1, s.reb.p);
+    else if (bf) MG_CS(2, 0, s.reb.p);
+    else if (ctile == 1) MG_CS(1, 1, s.re16.p);
+    else MG_CS(1, 0, s.re16.p);
+#undef MG_CS
+  });
+  MG_LAUNCH_CHECK();
+}
+
+void cgne_fused_start(const CoarseStore& DH, mgdwf_prec prec, int ctile, const float2* b, float2* r, float2* p,
+                      void* work, double* sl, int rr0, int cur, int tmp, const CoarseGeometry& cg, int nrhs,
+                      hipStream_t st) {
+  double *part_r, *part_p;
+  CgneStep q = cgne_carve(work, cg, nrhs, nullptr, r, p, &part_r, &part_p);
+  q.part_out = part_r;
+  const long long nsv = (long long)nrhs * cg.Vc;
+  with_n2(cg.n2, [&](auto N) {
+    constexpr int N2 = decltype(N)::value;
+    const dim3 grid(ceil_div(nsv, 4));
+    if (prec == MGDWF_F32) hipLaunchKernelGGL((k_cgne_start<0, N2>), grid, dim3(256), 0, st, b, q, nsv);
+    else if (prec == MGDWF_BF16) hipLaunchKernelGGL((k_cgne_start<2, N2>), grid, dim3(256), 0, st, b, q, nsv);
+    else hipLaunchKernelGGL((k_cgne_start<1, N2>), grid, dim3(256), 0, st, b, q, nsv);
+  });
+  MG_LAUNCH_CHECK();
+  cgne_partials(q, part_r, cg, nrhs, sl, tmp, st);
+  q.part_out = part_p;
+  q.first = 1;
+  q.cur = q.nxt = cur;  // |r|^2 -> cur and rr0
+  q.aux = rr0;
+  cgne_launch<1>(DH, prec, ctile, q, cg, nrhs, st);
+}
+
+void cgne_fused_rstep(const CoarseStore& D, mgdwf_prec prec, int ctile, float2* x, float2* r, float2* p, void* work,
+                      double* sl, int cur, int tmp, bool first, const CoarseGeometry& cg, int nrhs, hipStream_t st) {
+  double *part_r, *part_p;
+  CgneStep q = cgne_carve(work, cg, nrhs, x, r, p, &part_r, &part_p);
+  cgne_partials(q, part_p, cg, nrhs, sl, tmp, st);
+  q.part_out = part_r;
+  q.first = first ? 1 : 0;
+  q.cur = q.nxt = cur;
+  cgne_launch<0>(D, prec, ctile, q, cg, nrhs, st);
+}
+
+void cgne_fused_pstep(const CoarseStore& DH, mgdwf_prec prec, int ctile, float2* r, float2* p, void* work, double* sl,
+                      int cur, int nxt, int tmp, const CoarseGeometry& cg, int nrhs, hipStream_t st) {
+  double *part_r, *part_p;
+  CgneStep q = cgne_carve(work, cg, nrhs, nullptr, r, p, &part_r, &part_p);
+  cgne_partials(q, part_r, cg, nrhs, sl, tmp, st);
+  q.part_out = part_p;
+  q.cur = cur;
+  q.nxt = nxt;
+  cgne_launch<1>(DH, prec, ctile, q, cg, nrhs, st);
 }
 
 size_t persistent_cgne_bytes(const CoarseGeometry& cg, int nrhs) {
@@ -718,8 +1034,12 @@ bool coarse_cgne_persistent(const CoarseStore& D, const CoarseStore& DH, mgdwf_p
       maxiter < 1)
     return false;
   const bool bf = prec == MGDWF_BF16;
-  const void* fn = bf ? reinterpret_cast<const void*>(&k_cgne_persistent<true>)
-                      : reinterpret_cast<const void*>(&k_cgne_persistent<false>);
+  const void* fn = nullptr;
+  with_n2(cg.n2, [&](auto N) {
+    constexpr int N2 = decltype(N)::value;
+    fn = bf ? reinterpret_cast<const void*>(&k_cgne_persistent<true, N2>)
+            : reinterpret_cast<const void*>(&k_cgne_persistent<false, N2>);
+  });
   int coop = 0, ncu = 0, per_cu = 0, clock_khz = 0;
   MG_HIP(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, device));
   MG_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device));

@@ -176,12 +176,39 @@ struct TwoLevel {
   static constexpr int check = 8;
 
   void cg_iteration(F2* x, int it, int cur, int nxt) {
+    if constexpr (std::is_same<F2, float2>::value) {
+      if (cgne_fused(c->cg, p.coarse_prec)) {
+        char* work = c->buf<char>("vc_cgne", cgne_fused_bytes(c->cg, nrhs));
+        cgne_fused_rstep(c->Dc, p.coarse_prec, c->g.ctile, x, cr, cp, work, sl, cur, S_CPP, it == 0, c->cg, nrhs, c->st);
+        cgne_fused_pstep(c->DcH, p.coarse_prec, c->g.ctile, cr, cp, work, sl, cur, nxt, S_CPP, c->cg, nrhs, c->st);
+        c->coarse_applies += 2;
+        return;
+      }
+    }
     coarse_op(c, p, cp, cq, false, nrhs);
     mr_update<F2>(x, cr, cp, cq, nc, nrhs, sl, cur, S_CPP, it == 0, vpart, c->st);
     finalize_rhs(vpart, vec_blocks(nc), 1, sl, nxt, nrhs, c->st);
     coarse_op(c, p, cr, ct, true, nrhs);
     cg_dir<F2>(cp, ct, nc, nrhs, sl, nxt, cur, vpart, c->st);
     finalize_rhs(vpart, vec_blocks(nc), 1, sl, S_CPP, nrhs, c->st);
+  }
+
+  // r = b, p = D_c^+ r, |r|^2 and |p|^2
+  void cg_start(const F2* b) {
+    if constexpr (std::is_same<F2, float2>::value) {
+      if (cgne_fused(c->cg, p.coarse_prec)) {
+        char* work = c->buf<char>("vc_cgne", cgne_fused_bytes(c->cg, nrhs));
+        cgne_fused_start(c->DcH, p.coarse_prec, c->g.ctile, b, cr, cp, work, sl, S_CRR0, S_CRR_A, S_CPP, c->cg, nrhs,
+                         c->st);
+        c->coarse_applies += 1;
+        return;
+      }
+    }
+    copy(c, b, cr, nc * nrhs);
+    norm_into<F2>(c, cr, nullptr, nc, nrhs, S_CRR0);
+    norm_into<F2>(c, cr, nullptr, nc, nrhs, S_CRR_A);
+    coarse_op(c, p, cr, cp, true, nrhs);
+    norm_into<F2>(c, cp, nullptr, nc, nrhs, S_CPP);
   }
 
   // Capture `body` (launches only, no host synchronisation, every workspace
@@ -291,11 +318,7 @@ struct TwoLevel {
       }
       ++c->persist_fallbacks;  // not applicable here: the launched loop below
     }
-    copy(c, b, cr, nc * nrhs);
-    norm_into<F2>(c, cr, nullptr, nc, nrhs, S_CRR0);
-    norm_into<F2>(c, cr, nullptr, nc, nrhs, S_CRR_A);
-    coarse_op(c, p, cr, cp, true, nrhs);
-    norm_into<F2>(c, cp, nullptr, nc, nrhs, S_CPP);
+    cg_start(b);
     int cur = S_CRR_A, nxt = S_CRR_B;
     const double tol2 = p.coarse_tol * p.coarse_tol;
     int it = 0;

@@ -84,9 +84,25 @@ void finish_coarse_op(CoarseStore& Dc, CoarseStore& DcH, const CoarseGeometry& c
 void coarse_apply64(const CoarseStore& s, const double2* x, double2* y, const CoarseGeometry& cg, int nrhs,
                     hipStream_t st);
 size_t coarse_pack_bytes(const CoarseGeometry& cg, int nrhs);
-// ctile: MFMA shape of the 16-bit apply, 0 = 16x16x16, 1 = 16x16x32
-void coarse_apply32(const CoarseStore& s, mgdwf_prec prec, const float2* x, float2* y, const CoarseGeometry& cg,
+// ctile: MFMA shape of the 16-bit apply, 0 = 16x16x16, 1 = 16x16x32; the
+// vectors FP32 or FP64 complex (rounded to FP32 on the way in; FP64 input for
+// the 16-bit stores only, whose packing is the rounding)
+template <class I2, class O2>
+void coarse_apply32(const CoarseStore& s, mgdwf_prec prec, const I2* x, O2* y, const CoarseGeometry& cg,
                     int nrhs, void* pack, int ctile, hipStream_t st);
+// Coarse CGNE as two launches per iteration (F32, F16 and BF16 stores, 2 Nv a
+// multiple of 16).  work: cgne_fused_bytes.  start: r = b, p = D_c^+ r, |r|^2
+// into slots rr0 and cur; rstep: x (+)= alpha p, r -= alpha D_c p; pstep: |r|^2
+// into nxt, p = D_c^+ r + beta p.  tmp: a scratch slot.
+bool cgne_fused(const CoarseGeometry& cg, mgdwf_prec prec);
+size_t cgne_fused_bytes(const CoarseGeometry& cg, int nrhs);
+void cgne_fused_start(const CoarseStore& DH, mgdwf_prec prec, int ctile, const float2* b, float2* r, float2* p,
+                      void* work, double* sl, int rr0, int cur, int tmp, const CoarseGeometry& cg, int nrhs,
+                      hipStream_t st);
+void cgne_fused_rstep(const CoarseStore& D, mgdwf_prec prec, int ctile, float2* x, float2* r, float2* p, void* work,
+                      double* sl, int cur, int tmp, bool first, const CoarseGeometry& cg, int nrhs, hipStream_t st);
+void cgne_fused_pstep(const CoarseStore& DH, mgdwf_prec prec, int ctile, float2* r, float2* p, void* work, double* sl,
+                      int cur, int nxt, int tmp, const CoarseGeometry& cg, int nrhs, hipStream_t st);
 // Coarse CGNE (x = D_c^+ y, D_c D_c^+ y = b, from x = 0, to |r| <= tol |b| tested
 // every 8 iterations, or maxiter iterations) as one persistent cooperative
 // launch on the 16-bit store, at most one workgroup per CU, each owning

@@ -214,6 +214,17 @@ __global__ void k_dc_canonical(const double2* __restrict__ in, double2* __restri
   out[i] = in[blk * n2 * n2 + (long long)col * n2 + row];
 }
 
+// y = D x through the internal layout (workspaces a, b)
+template <class F2>
+void apply_packed(mgdwf_handle h, const double2* x, double2* y, bool dagger, int nrhs, F2* a, F2* b) {
+  pack_field(h, x, a, nrhs);
+  fine_dslash<F2>(h, a, b, nullptr, dagger, 0, nrhs, nullptr, h->st);
+  unpack_field(h, b, y, nrhs);
+}
+
+// complex numbers up to which an FP32 application runs on the canonical fields
+constexpr long long kCanonicalF32 = 1 << 20;
+
 // y = D_c x in a reduced precision on canonical FP64 vectors: an FP32 copy of x
 // (a32) or its 16-bit packing (pack) first, so x and y may be one buffer
 void coarse_apply_reduced(mgdwf_handle h, const CoarseStore& s, mgdwf_prec prec, const double2* x, double2* y, int nrhs,
@@ -342,20 +353,24 @@ mgdwf_status mgdwf_apply_dwf(mgdwf_handle h, const double* in, double* out, int3
     need(nrhs >= 1, MGDWF_ERR_INVALID_ARG, "nrhs must be >= 1");
     check_prec_fine(prec);
     need(h->have_gauge, MGDWF_ERR_STATE, "gauge field not set");
+    const double2* x = reinterpret_cast<const double2*>(in);
+    double2* y = reinterpret_cast<double2*>(out);
     const long long n = h->fine_len() * nrhs;
-    double2* a = h->buf<double2>("io_a", n);
-    double2* b = h->buf<double2>("io_b", n);
-    pack_field(h, reinterpret_cast<const double2*>(in), a, nrhs);
-    if (prec == MGDWF_F64) {
-      fine_dslash<double2>(h, a, b, nullptr, dagger != 0, 0, nrhs, nullptr, h->st);
+    // One launch on the canonical fields where that is faster than packing, the
+    // internal-layout kernel and unpacking: in FP64 everywhere (16^3x32x16, 12
+    // fields: 6.7 against 8.8 ms; 4^4x8: 5.0 against 12 us); in FP32, whose
+    // internal-layout kernels are the tiled ones, on small fields (4^4x8: 4.9
+    // against 15.3 us; 9x7x5x11x5, 3 fields: 16.2 against 21.5; 8^3x16x16, one
+    // field of 1.6e6 numbers: 30.5 against 28.4), unless a tiling was chosen
+    if (h->model == 0 && prec == MGDWF_F64) {
+      dslash_canonical<double2>(x, y, h->U64.as<double2>(), h->g, h->M5, h->mf, dagger != 0, nrhs, h->st);
+    } else if (h->model == 0 && h->g.ftile < 0 && n <= kCanonicalF32) {
+      dslash_canonical<float2>(x, y, h->U32.as<float2>(), h->g, h->M5, h->mf, dagger != 0, nrhs, h->st);
+    } else if (prec == MGDWF_F64) {
+      apply_packed<double2>(h, x, y, dagger != 0, nrhs, h->buf<double2>("io_a", n), h->buf<double2>("io_b", n));
     } else {
-      float2* a32 = h->buf<float2>("io_a32", n);
-      float2* b32 = h->buf<float2>("io_b32", n);
-      convert<double2, float2>(a, a32, n, h->st);
-      fine_dslash<float2>(h, a32, b32, nullptr, dagger != 0, 0, nrhs, nullptr, h->st);
-      convert<float2, double2>(b32, b, n, h->st);
+      apply_packed<float2>(h, x, y, dagger != 0, nrhs, h->buf<float2>("io_a32", n), h->buf<float2>("io_b32", n));
     }
-    unpack_field(h, b, reinterpret_cast<double2*>(out), nrhs);
   });
 }
 
@@ -405,15 +420,15 @@ mgdwf_status mgdwf_restrict(mgdwf_handle h, const double* fine, double* coarse, 
     check_prec_fine(prec);
     need(h->have_basis, MGDWF_ERR_STATE, "no basis installed");
     const long long n = h->fine_len() * nrhs;
-    double2* a = h->buf<double2>("io_a", n);
-    pack_field(h, reinterpret_cast<const double2*>(fine), a, nrhs);
     if (prec == MGDWF_F64) {
+      double2* a = h->buf<double2>("io_a", n);
+      pack_field(h, reinterpret_cast<const double2*>(fine), a, nrhs);
       fine_restrict<double2>(h, h->V64.as<double2>(), a, reinterpret_cast<double2*>(coarse), nrhs);
     } else {
       const long long nc = h->coarse_len() * nrhs;
       float2* a32 = h->buf<float2>("io_a32", n);
       float2* c32 = h->buf<float2>("io_c32", nc);
-      convert<double2, float2>(a, a32, n, h->st);
+      pack_field(h, reinterpret_cast<const double2*>(fine), a32, nrhs);
       fine_restrict<float2>(h, h->V32.as<float2>(), a32, c32, nrhs);
       convert<float2, double2>(c32, reinterpret_cast<double2*>(coarse), nc, h->st);
     }
@@ -426,18 +441,18 @@ mgdwf_status mgdwf_prolong(mgdwf_handle h, const double* coarse, double* fine, i
     check_prec_fine(prec);
     need(h->have_basis, MGDWF_ERR_STATE, "no basis installed");
     const long long n = h->fine_len() * nrhs;
-    double2* a = h->buf<double2>("io_a", n);
     if (prec == MGDWF_F64) {
+      double2* a = h->buf<double2>("io_a", n);
       fine_prolong<double2>(h, h->V64.as<double2>(), reinterpret_cast<const double2*>(coarse), a, false, nrhs);
+      unpack_field(h, a, reinterpret_cast<double2*>(fine), nrhs);
     } else {
       const long long nc = h->coarse_len() * nrhs;
       float2* a32 = h->buf<float2>("io_a32", n);
       float2* c32 = h->buf<float2>("io_c32", nc);
       convert<double2, float2>(reinterpret_cast<const double2*>(coarse), c32, nc, h->st);
       fine_prolong<float2>(h, h->V32.as<float2>(), c32, a32, false, nrhs);
-      convert<float2, double2>(a32, a, n, h->st);
+      unpack_field(h, a32, reinterpret_cast<double2*>(fine), nrhs);
     }
-    unpack_field(h, a, reinterpret_cast<double2*>(fine), nrhs);
   });
 }
 mgdwf_status mgdwf_build_coarse(mgdwf_handle h) {
@@ -633,10 +648,10 @@ mgdwf_status mgdwf_low_modes(mgdwf_handle h, const double* v0, int32_t nev, int3
     need(h->have_coarse && h->have_params, MGDWF_ERR_STATE, "the Lanczos steps solve with the multigrid: set it up first");
     const long long nf = h->fine_len();
     double2* a = h->buf<double2>("io_a", nf);
-    pack_fermion_f64(reinterpret_cast<const double2*>(v0), a, h->g, 1, h->st);
+    pack_field(h, reinterpret_cast<const double2*>(v0), a, 1);
     double2* ev = evecs ? h->buf<double2>("lm_evecs", (size_t)nev * nf) : nullptr;
     low_modes(h, a, nev, m, solve_tol, evals, ev, resid);
-    if (evecs) unpack_fermion_f64(ev, reinterpret_cast<double2*>(evecs), h->g, nev, h->st);
+    if (evecs) unpack_field(h, ev, reinterpret_cast<double2*>(evecs), nev);
     MG_HIP(hipStreamSynchronize(h->st));
     for (auto it = h->ws.begin(); it != h->ws.end();)  // the Krylov basis is large: give it back
       it = it->first.rfind("lm_", 0) == 0 ? h->ws.erase(it) : std::next(it);

@@ -248,8 +248,9 @@ __device__ __forceinline__ uint4 negate16(uint4 v) {
 // of one round of loads (few sites) or by the bytes of M (many): N2 is a
 // template argument, so every load of the round is issued before the first
 // product waits for one.  With N2 at run time each tile's load waited for the
-// one before it: at 48 dof 12.6 us on 32 sites and 25.8 us on 512, one
-// right-hand side, against MNEW here.
+// one before it: at 48 dof and FP16, 12.6 us on 32 sites (12 right-hand sides)
+// and 25.8 us on 512 (one), against 8.4 and 11.9 us for the CGNE steps below,
+// whose vector updates and sums are included.
 // Each wavefront leaves its tiles in its slab of LDS ([col][row], Re rows then
 // Im rows); slab_sum adds the nine in a fixed order.
 template <int N2> __host__ __device__ constexpr int slab_stride() { return 2 * N2 + 4; }

@@ -117,8 +117,8 @@ namespace mgdwf {
 
 // Fine-level operations of the handle's model (u1_2d.hip): the 4D kernels for
 // model 0, the 2D ones for model 1.
-void pack_field(const mgdwf_ctx* c, const double2* canon, double2* field, int nrhs);
-void unpack_field(const mgdwf_ctx* c, const double2* field, double2* canon, int nrhs);
+template <class F2> void pack_field(const mgdwf_ctx* c, const double2* canon, F2* field, int nrhs);
+template <class F2> void unpack_field(const mgdwf_ctx* c, const F2* field, double2* canon, int nrhs);
 // allocates and fills U64 / U32 in the model's internal gauge layouts
 void pack_gauge_field(mgdwf_ctx* c, const double2* canon);
 // workgroups (partial sums per right-hand side) of fine_dslash with a partial buffer

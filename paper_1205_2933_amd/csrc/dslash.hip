@@ -15,6 +15,8 @@
 // has rank 2 in spin, so two SU(3) mat-vecs per direction instead of four.
 // Workgroup indices are remapped so each XCD sweeps a contiguous slab of the
 // lattice and neighbour re-reads hit its own L2.
+#include <type_traits>
+
 #include "mg_internal.h"
 #include "blas.h"
 
@@ -145,79 +147,115 @@ struct DslashArgs {
   double mf;
 };
 
+// The plain kernel, for every lattice and both precisions.  A workgroup covers
+// 64 consecutive 5D sites (x4, s); its four wavefronts take the same sites, one
+// direction mu each (both hops), leave their sums in LDS, and then take one
+// spin each for the diagonal, the fifth dimension and the store.
+// Bound by the latency of its one round of loads on small lattices (4^4x8, FP64:
+// 3.9 us, 8.8 with one thread per site and all eight hops in a row), by L2 reads
+// on large ones (16^3x32x16, FP64: 410 us per field, every neighbour and link
+// loaded by every lane; links staged once per site in LDS: 485 us).
+// CANON: in and out are canonical FP64 fields (site major, all 12 components of
+// a site together), converted on the way, so a call on a small lattice is one
+// launch.
+template <class C2, bool CANON>
+struct FieldIO {
+  using IO = typename std::conditional<CANON, double2, C2>::type;
+  using T = typename real_of<C2>::type;
+  static __device__ __forceinline__ C2 get(const IO* __restrict__ f, int c, long long V5, long long i5) {
+    const IO v = CANON ? f[i5 * 12 + c] : f[c * V5 + i5];
+    return cmk<C2>((T)v.x, (T)v.y);
+  }
+  static __device__ __forceinline__ void put(IO* __restrict__ f, int c, long long V5, long long i5, C2 v) {
+    f[CANON ? i5 * 12 + c : c * V5 + i5] = cmk<IO>(v.x, v.y);
+  }
+};
+
+// both hops of direction MU at (x4, s) into acc
+template <int MU, bool DAG, class C2, bool CANON>
+__device__ __forceinline__ void hops_mu(Spinor<C2>& acc, const typename FieldIO<C2, CANON>::IO* __restrict__ in,
+                                        const C2* __restrict__ gauge, const DslashArgs& a, int x4, int s) {
+  constexpr int EF = DAG ? 1 : -1, EB = DAG ? -1 : 1;
+  const int st = MU == 0 ? 1 : (MU == 1 ? a.L[0] : (MU == 2 ? a.L[0] * a.L[1] : a.L[0] * a.L[1] * a.L[2]));
+  const int co = (x4 / st) % a.L[MU];
+  const bool top = co == a.L[MU] - 1, bot = co == 0;
+  const int xf = top ? x4 - (a.L[MU] - 1) * st : x4 + st;
+  const int xb = bot ? x4 + (a.L[MU] - 1) * st : x4 - st;
+  Spinor<C2> pf, pb;
+#pragma unroll
+  for (int c = 0; c < 12; ++c) {
+    pf.v[c / 3][c % 3] = FieldIO<C2, CANON>::get(in, c, a.V5, (long long)xf * a.Ls + s);
+    pb.v[c / 3][c % 3] = FieldIO<C2, CANON>::get(in, c, a.V5, (long long)xb * a.Ls + s);
+  }
+#pragma unroll
+  for (int c = 0; c < 12; ++c) acc.v[c / 3][c % 3] = cmk<C2>(0, 0);
+  C2 h[2][3], u[2][3];
+  project<MU, EF>(pf, h);
+  transport<false>(gauge, MU, (long long)a.V4, x4, h, u);
+  if (top && a.ph[MU] != 1.0f) {
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) u[r][c] = cscale(u[r][c], a.ph[MU]);
+  }
+  accumulate<MU, EF>(acc, u);
+  project<MU, EB>(pb, h);
+  transport<true>(gauge, MU, (long long)a.V4, xb, h, u);
+  if (bot && a.ph[MU] != 1.0f) {
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) u[r][c] = cscale(u[r][c], a.ph[MU]);
+  }
+  accumulate<MU, EB>(acc, u);
+}
+
 // MODE 0: out = D in;  MODE 1: out = b - D in.  partial (if non-null) gets the
 // per-workgroup sum of |out|^2 at index blockIdx.y * gridDim.x + blockIdx.x.
-template <class C2, bool DAG, int MODE>
-__global__ __launch_bounds__(256) void k_dslash(const C2* __restrict__ in, C2* __restrict__ out,
-                                                const C2* __restrict__ b, const C2* __restrict__ gauge,
-                                                DslashArgs a, double* __restrict__ partial) {
+template <class C2, bool CANON, bool DAG, int MODE>
+__global__ __launch_bounds__(256) void k_dslash(const typename FieldIO<C2, CANON>::IO* __restrict__ in,
+                                                typename FieldIO<C2, CANON>::IO* __restrict__ out,
+                                                const C2* __restrict__ b, const C2* __restrict__ gauge, DslashArgs a,
+                                                double* __restrict__ partial) {
   using T = typename real_of<C2>::type;
+  using IO = FieldIO<C2, CANON>;
+  __shared__ C2 sm[4][12][64];
   const int bid = xcd_remap(blockIdx.x, gridDim.x);
-  const long long i5 = (long long)bid * 256 + threadIdx.x;
-  const long long V5 = a.V5, V4 = a.V4;
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), l = threadIdx.x & 63;
+  const long long V5 = a.V5, i5 = (long long)bid * 64 + l;
   const long long roff = (long long)blockIdx.y * 12 * V5;
   in += roff;
   out += roff;
   if (MODE == 1) b += roff;
+  const int Ls = a.Ls;
+  const int x4 = (int)(i5 / Ls), s = (int)(i5 - (long long)x4 * Ls);
+  if (i5 < V5) {
+    Spinor<C2> acc;
+    if (w == 0) hops_mu<0, DAG, C2, CANON>(acc, in, gauge, a, x4, s);
+    else if (w == 1) hops_mu<1, DAG, C2, CANON>(acc, in, gauge, a, x4, s);
+    else if (w == 2) hops_mu<2, DAG, C2, CANON>(acc, in, gauge, a, x4, s);
+    else hops_mu<3, DAG, C2, CANON>(acc, in, gauge, a, x4, s);
+#pragma unroll
+    for (int c = 0; c < 12; ++c) sm[w][c][l] = acc.v[c / 3][c % 3];
+  }
+  __syncthreads();
   double nrm = 0.0;
   if (i5 < V5) {
-    const int Ls = a.Ls;
-    const int x4 = (int)(i5 / Ls);
-    const int s = (int)(i5 - (long long)x4 * Ls);
-    int co[4];
-    {
-      int r = x4;
-      co[0] = r % a.L[0]; r /= a.L[0];
-      co[1] = r % a.L[1]; r /= a.L[1];
-      co[2] = r % a.L[2]; co[3] = r / a.L[2];
+    // spin w: coupled to s + 1 are {2,3} for D, {0,1} for D^+; the others to s - 1
+    const bool up = DAG ? w < 2 : w >= 2;
+    const bool wall = up ? s == Ls - 1 : s == 0;
+    const int sn = up ? (wall ? 0 : s + 1) : (wall ? Ls - 1 : s - 1);
+    const T cn = wall ? (T)a.mf : (T)-1, half = (T)-0.5, dg = (T)a.diag;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const int c = w * 3 + q;
+      const C2 hop = cadd(cadd(cadd(sm[0][c][l], sm[1][c][l]), sm[2][c][l]), sm[3][c][l]);
+      C2 r = cadd(cscale(IO::get(in, c, V5, i5), dg), cscale(hop, half));
+      r = cadd(r, cscale(IO::get(in, c, V5, (long long)x4 * Ls + sn), cn));
+      if (MODE == 1) r = csub(b[c * V5 + i5], r);
+      IO::put(out, c, V5, i5, r);
+      nrm += (double)r.x * r.x + (double)r.y * r.y;
     }
-    int stride[4] = {1, a.L[0], a.L[0] * a.L[1], a.L[0] * a.L[1] * a.L[2]};
-    int xf[4], xb[4];
-    float phf[4], phb[4];
-#pragma unroll
-    for (int mu = 0; mu < 4; ++mu) {
-      bool top = co[mu] == a.L[mu] - 1, bot = co[mu] == 0;
-      xf[mu] = top ? x4 - (a.L[mu] - 1) * stride[mu] : x4 + stride[mu];
-      xb[mu] = bot ? x4 + (a.L[mu] - 1) * stride[mu] : x4 - stride[mu];
-      phf[mu] = top ? a.ph[mu] : 1.0f;
-      phb[mu] = bot ? a.ph[mu] : 1.0f;
-    }
-    Spinor<C2> acc;
-#pragma unroll
-    for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) acc.v[sp][c] = cmk<C2>(0, 0);
-    // D: forward (1 - g), backward (1 + g);  D^+: the other way round
-    constexpr int EF = DAG ? 1 : -1;
-    constexpr int EB = DAG ? -1 : 1;
-    hop_dir<0, EF, EB>(acc, in, gauge, V5, V4, Ls, s, x4, xf[0], xb[0], phf[0], phb[0]);
-    hop_dir<1, EF, EB>(acc, in, gauge, V5, V4, Ls, s, x4, xf[1], xb[1], phf[1], phb[1]);
-    hop_dir<2, EF, EB>(acc, in, gauge, V5, V4, Ls, s, x4, xf[2], xb[2], phf[2], phb[2]);
-    hop_dir<3, EF, EB>(acc, in, gauge, V5, V4, Ls, s, x4, xf[3], xb[3], phf[3], phb[3]);
-
-    // fifth dimension: spins coupled to s+1 are {2,3} for D, {0,1} for D^+
-    const int up0 = DAG ? 0 : 2;
-    const int dn0 = DAG ? 2 : 0;
-    const long long base = (long long)x4 * Ls;
-    const int sp1 = (s == Ls - 1) ? 0 : s + 1;
-    const int sm1 = (s == 0) ? Ls - 1 : s - 1;
-    const T cup = (s == Ls - 1) ? (T)a.mf : (T)-1;
-    const T cdn = (s == 0) ? (T)a.mf : (T)-1;
-    const T half = (T)-0.5;
-    const T dg = (T)a.diag;
-#pragma unroll
-    for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) {
-        const long long cc = (long long)(sp * 3 + c) * V5;
-        C2 self = in[cc + i5];
-        C2 r = cadd(cscale(self, dg), cscale(acc.v[sp][c], half));
-        if (sp == up0 || sp == up0 + 1) r = cadd(r, cscale(in[cc + base + sp1], cup));
-        if (sp == dn0 || sp == dn0 + 1) r = cadd(r, cscale(in[cc + base + sm1], cdn));
-        if (MODE == 1) r = csub(b[cc + i5], r);
-        out[cc + i5] = r;
-        nrm += (double)r.x * r.x + (double)r.y * r.y;
-      }
   }
   if (partial) {
     double sum = block_sum<256>(nrm);
@@ -2150,7 +2188,7 @@ int dslash_nblocks(const Geometry& g, int nrhs) {
     case DS_TMARCH:
       return (g.L[0] / TMX) * (g.L[1] / TMY) * (g.L[2] / TMZ) * ceil_div(g.L[3], tmarch_chunk(g));
     default:
-      return ceil_div(g.V5, 256);
+      return ceil_div(g.V5, 64);
   }
 }
 template int dslash_nblocks<double2>(const Geometry&, int);
@@ -2217,7 +2255,7 @@ void dslash_ex(const C2* in, C2* out, const C2* b, const C2* gauge, const Geomet
   }
   dim3 grid(dslash_nblocks<C2>(g, nrhs), nrhs), blk(256);
 #define MG_DS(DAG, MODE) \
-  hipLaunchKernelGGL((k_dslash<C2, DAG, MODE>), grid, blk, 0, st, in, out, b, gauge, a, partial)
+  hipLaunchKernelGGL((k_dslash<C2, false, DAG, MODE>), grid, blk, 0, st, in, out, b, gauge, a, partial)
   if (!dagger && mode == 0) MG_DS(false, 0);
   else if (!dagger && mode == 1) MG_DS(false, 1);
   else if (dagger && mode == 0) MG_DS(true, 0);
@@ -2225,6 +2263,24 @@ void dslash_ex(const C2* in, C2* out, const C2* b, const C2* gauge, const Geomet
 #undef MG_DS
   MG_LAUNCH_CHECK();
 }
+
+template <class C2>
+void dslash_canonical(const double2* in, double2* out, const C2* gauge, const Geometry& g, double M5, double mf,
+                      bool dagger, int nrhs, hipStream_t st) {
+  DslashArgs a;
+  for (int m = 0; m < 4; ++m) { a.L[m] = g.L[m]; a.ph[m] = (float)g.bc[m]; }
+  a.Ls = g.Ls; a.V4 = g.V4; a.V5 = g.V5; a.diag = 5.0 - M5; a.mf = mf;
+  const dim3 grid(ceil_div(g.V5, 64), nrhs), blk(256);
+  if (dagger)
+    hipLaunchKernelGGL((k_dslash<C2, true, true, 0>), grid, blk, 0, st, in, out, nullptr, gauge, a, nullptr);
+  else
+    hipLaunchKernelGGL((k_dslash<C2, true, false, 0>), grid, blk, 0, st, in, out, nullptr, gauge, a, nullptr);
+  MG_LAUNCH_CHECK();
+}
+template void dslash_canonical<double2>(const double2*, double2*, const double2*, const Geometry&, double, double, bool,
+                                        int, hipStream_t);
+template void dslash_canonical<float2>(const double2*, double2*, const float2*, const Geometry&, double, double, bool,
+                                       int, hipStream_t);
 
 template <class C2>
 void dslash(const C2* in, C2* out, const C2* b, const C2* gauge, const Geometry& g, double M5,

@@ -109,15 +109,20 @@ __device__ __forceinline__ int xcd_remap(int bid, int nblocks) {
 
 // ---------------------------------------------------------------- kernels API
 // layout / conversion
-void pack_fermion_f64(const double2* canon, double2* field, const Geometry& g, int nrhs, hipStream_t st);
-void unpack_fermion_f64(const double2* field, double2* canon, const Geometry& g, int nrhs, hipStream_t st);
+template <class F2>
+void pack_fermion(const double2* canon, F2* field, const Geometry& g, int nrhs, hipStream_t st);
+template <class F2>
+void unpack_fermion(const F2* field, double2* canon, const Geometry& g, int nrhs, hipStream_t st);
 void pack_gauge(const double2* canon, double2* g64, float2* g32, const Geometry& g, hipStream_t st);
-void convert_f64_to_f32(const double2* in, float2* out, long long n, hipStream_t st);
-void convert_f32_to_f64(const float2* in, double2* out, long long n, hipStream_t st);
 
 // Dslash:  out = D in  (dagger: D^+).  mode 0: out = D in;  mode 1: out = b - D in.
 template <class R2>
 void dslash(const R2* in, R2* out, const R2* b, const R2* gauge, const Geometry& g, double M5,
             double mf, bool dagger, int mode, int nrhs, hipStream_t st);
+
+// the same on canonical FP64 fields in one launch (computed in C2's precision)
+template <class C2>
+void dslash_canonical(const double2* in, double2* out, const C2* gauge, const Geometry& g, double M5, double mf,
+                      bool dagger, int nrhs, hipStream_t st);
 
 }  // namespace mgdwf

@@ -399,9 +399,7 @@ void net_propose(NullNet& net, mgdwf_ctx* c, const double2* eta, double2* V_cano
   hipLaunchKernelGGL(k_lift, dim3(nb((long long)nh * V4 * Ls)), dim3(256), 0, c->st, c->buf<float2>("nn_pre3", 0),
                      v32, V4, Ls, (float)(1.0 - c->M5), nh);
   MG_LAUNCH_CHECK();
-  double2* v64 = c->buf<double2>("nn_v64", nf * nh);
-  convert<float2, double2>(v32, v64, nf * nh, c->st);
-  unpack_fermion_f64(v64, V_canon, c->g, nh, c->st);
+  unpack_fermion(v32, V_canon, c->g, nh, c->st);
   MG_HIP(hipStreamSynchronize(c->st));
 }
 

@@ -21,6 +21,8 @@
 //   gauge: element (mu, x2) at mu * Lx * Ly + x2 (FP64 in U64, FP32 in U32).
 #include <functional>
 
+#include <type_traits>
+
 #include "blas.h"
 #include "ctx.h"
 #include "vecops.h"
@@ -114,16 +116,18 @@ __global__ __launch_bounds__(256) void k_dwf2d(const F2* __restrict__ in, F2* __
   }
 }
 
-// canonical ((x2 * Ls + s) * 2 + spin) <-> internal ((x2 * 2 + spin) * Ls + s)
-__global__ void k_pack2d(const double2* __restrict__ canon, double2* __restrict__ field, int Ls, long long n,
-                         int unpack) {
+// canonical ((x2 * Ls + s) * 2 + spin, FP64) <-> internal ((x2 * 2 + spin) * Ls + s, FP64 or FP32)
+template <class F2, bool UNPACK>
+__global__ void k_pack2d(typename std::conditional<UNPACK, double2, const double2>::type* __restrict__ canon,
+                         typename std::conditional<UNPACK, const F2, F2>::type* __restrict__ field, int Ls, long long n) {
+  using T = typename real_of<F2>::type;
   for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (long long)gridDim.x * blockDim.x) {
     const long long site = e / (2 * Ls);
     const int r = (int)(e - site * 2 * Ls);
     const int s = r >> 1, sp = r & 1;
     const long long f = (site * 2 + sp) * Ls + s;
-    if (unpack) field[e] = canon[f];  // here `canon` is the internal field, `field` the canonical output
-    else field[f] = canon[e];
+    if constexpr (UNPACK) canon[e] = make_double2(field[f].x, field[f].y);
+    else field[f] = cmk<F2>((T)canon[e].x, (T)canon[e].y);
   }
 }
 
@@ -175,25 +179,31 @@ void dwf2d(const mgdwf_ctx* c, const F2* in, F2* out, const F2* b, bool dag, int
 
 // ---------------------------------------------------------------- model dispatch
 
-void pack_field(const mgdwf_ctx* c, const double2* canon, double2* field, int nrhs) {
+template <class F2>
+void pack_field(const mgdwf_ctx* c, const double2* canon, F2* field, int nrhs) {
   if (c->model == 0) {
-    pack_fermion_f64(canon, field, c->g, nrhs, c->st);
+    pack_fermion<F2>(canon, field, c->g, nrhs, c->st);
     return;
   }
-  const long long n = 2LL * c->g.V5 * nrhs;
-  hipLaunchKernelGGL(k_pack2d, dim3(nblk(n)), dim3(256), 0, c->st, canon, field, c->g.Ls, n, 0);
+  const long long n = c->fine_len() * nrhs;
+  hipLaunchKernelGGL((k_pack2d<F2, false>), dim3(nblk(n)), dim3(256), 0, c->st, canon, field, c->g.Ls, n);
   MG_LAUNCH_CHECK();
 }
 
-void unpack_field(const mgdwf_ctx* c, const double2* field, double2* canon, int nrhs) {
+template <class F2>
+void unpack_field(const mgdwf_ctx* c, const F2* field, double2* canon, int nrhs) {
   if (c->model == 0) {
-    unpack_fermion_f64(field, canon, c->g, nrhs, c->st);
+    unpack_fermion<F2>(field, canon, c->g, nrhs, c->st);
     return;
   }
-  const long long n = 2LL * c->g.V5 * nrhs;
-  hipLaunchKernelGGL(k_pack2d, dim3(nblk(n)), dim3(256), 0, c->st, field, canon, c->g.Ls, n, 1);
+  const long long n = c->fine_len() * nrhs;
+  hipLaunchKernelGGL((k_pack2d<F2, true>), dim3(nblk(n)), dim3(256), 0, c->st, canon, field, c->g.Ls, n);
   MG_LAUNCH_CHECK();
 }
+template void pack_field<double2>(const mgdwf_ctx*, const double2*, double2*, int);
+template void pack_field<float2>(const mgdwf_ctx*, const double2*, float2*, int);
+template void unpack_field<double2>(const mgdwf_ctx*, const double2*, double2*, int);
+template void unpack_field<float2>(const mgdwf_ctx*, const float2*, double2*, int);
 
 void pack_gauge_field(mgdwf_ctx* c, const double2* canon) {
   if (c->model == 0) {

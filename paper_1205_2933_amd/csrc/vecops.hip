@@ -18,13 +18,17 @@ namespace {
 
 __device__ __forceinline__ double slot(const double* sl, int rhs, int i) { return sl[rhs * NSLOT + i]; }
 
-// out[rhs * NSLOT + dst + comp] = sum_i partial[(rhs * nparts + i) * ncomp + comp]
-__global__ void k_finalize_rhs(const double* __restrict__ partial, int nparts, int ncomp,
-                               double* __restrict__ sl, int dst) {
+// out[rhs * NSLOT + dst + comp] = sum_i partial[(rhs * nparts + i) * ncomp + comp].
+// One workgroup per sum, bound by load latency: BS 1024 and eight loads in
+// flight where there are many partials (the plain Dslash leaves V5 / 64).
+template <int BS>
+__global__ __launch_bounds__(BS) void k_finalize_rhs(const double* __restrict__ partial, int nparts, int ncomp,
+                                                     double* __restrict__ sl, int dst) {
   const int comp = blockIdx.x, rhs = blockIdx.y;
   double acc = 0.0;
-  for (int i = threadIdx.x; i < nparts; i += blockDim.x) acc += partial[((long long)rhs * nparts + i) * ncomp + comp];
-  acc = block_sum<256>(acc);
+#pragma unroll 8
+  for (int i = threadIdx.x; i < nparts; i += BS) acc += partial[((long long)rhs * nparts + i) * ncomp + comp];
+  acc = block_sum<BS>(acc);
   if (threadIdx.x == 0) sl[rhs * NSLOT + dst + comp] = acc;
 }
 
@@ -366,7 +370,10 @@ __global__ void k_reflect5(const C2* __restrict__ in, C2* __restrict__ out, long
 int vec_blocks(long long n) { return std::max(1, std::min(ceil_div(n, 256), VEC_BLOCKS)); }
 
 void finalize_rhs(const double* partial, int nparts, int ncomp, double* sl, int dst, int nrhs, hipStream_t st) {
-  hipLaunchKernelGGL(k_finalize_rhs, dim3(ncomp, nrhs), dim3(256), 0, st, partial, nparts, ncomp, sl, dst);
+  if (nparts > 2048)
+    hipLaunchKernelGGL(k_finalize_rhs<1024>, dim3(ncomp, nrhs), dim3(1024), 0, st, partial, nparts, ncomp, sl, dst);
+  else
+    hipLaunchKernelGGL(k_finalize_rhs<256>, dim3(ncomp, nrhs), dim3(256), 0, st, partial, nparts, ncomp, sl, dst);
   MG_LAUNCH_CHECK();
 }
 

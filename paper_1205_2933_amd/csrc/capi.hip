@@ -358,7 +358,7 @@ mgdwf_status mgdwf_apply_dwf(mgdwf_handle h, const double* in, double* out, int3
     const long long n = h->fine_len() * nrhs;
     // One launch on the canonical fields where that is faster than packing, the
     // internal-layout kernel and unpacking: in FP64 everywhere (16^3x32x16, 12
-    // fields: 6.7 against 8.8 ms; 4^4x8: 5.0 against 12 us); in FP32, whose
+    // fields: 4.4 against 7.1 ms; 4^4x8: 5.0 against 12 us); in FP32, whose
     // internal-layout kernels are the tiled ones, on small fields (4^4x8: 4.9
     // against 15.3 us; 9x7x5x11x5, 3 fields: 16.2 against 21.5; 8^3x16x16, one
     // field of 1.6e6 numbers: 30.5 against 28.4), unless a tiling was chosen
@@ -719,9 +719,9 @@ struct CkHeader {
   int64_t fine_len;
 };
 
-// FNV-1a over the bytes of the installed FP64 links (internal layout)
+// FNV-1a over the bytes of the installed FP64 links (internal layout, without a phase-folded copy behind them)
 uint64_t gauge_checksum(mgdwf_ctx* h) {
-  std::vector<unsigned char> host(h->U64.bytes);
+  std::vector<unsigned char> host((size_t)(h->model == 0 ? 36 : 2) * h->g.V4 * sizeof(double2));
   MG_HIP(hipMemcpyAsync(host.data(), h->U64.p, host.size(), hipMemcpyDeviceToHost, h->st));
   MG_HIP(hipStreamSynchronize(h->st));
   uint64_t x = 1469598103934665603ULL;

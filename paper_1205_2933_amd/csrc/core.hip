@@ -124,7 +124,7 @@ template void unpack_fermion<float2>(const float2*, double2*, const Geometry&, i
 
 // canonical gauge ((x4*4 + mu)*9 + ab) -> internal ((mu*9 + ab)*V4 + x4), FP64 and FP32
 __global__ void k_pack_gauge(const double2* __restrict__ canon, double2* __restrict__ g64,
-                             float2* __restrict__ g32, Geometry g) {
+                             float2* __restrict__ g32, Geometry g, int fold64) {
   const int V4 = g.V4;
   int x4 = blockIdx.x * blockDim.x + threadIdx.x;
   if (x4 >= V4) return;
@@ -134,6 +134,10 @@ __global__ void k_pack_gauge(const double2* __restrict__ canon, double2* __restr
     double2 v = canon[(long long)x4 * 36 + j];
     long long o = (long long)j * V4 + x4;
     g64[o] = v;
+    if (fold64) {  // second FP64 copy, folded as the third FP32 one
+      const double p64 = co[j / 9] == g.L[j / 9] - 1 ? (double)g.bc[j / 9] : 1.0;
+      g64[36LL * V4 + o] = make_double2(p64 * v.x, p64 * v.y);
+    }
     g32[o] = make_float2((float)v.x, (float)v.y);
     // second FP32 copy, site major ([x4][mu][a][b], the canonical order): the
     // 36 entries of a site are contiguous for the wavefront-per-site kernel
@@ -147,7 +151,8 @@ __global__ void k_pack_gauge(const double2* __restrict__ canon, double2* __restr
 }
 
 void pack_gauge(const double2* canon, double2* g64, float2* g32, const Geometry& g, hipStream_t st) {
-  hipLaunchKernelGGL(k_pack_gauge, dim3(ceil_div(g.V4, 256)), dim3(256), 0, st, canon, g64, g32, g);
+  hipLaunchKernelGGL(k_pack_gauge, dim3(ceil_div(g.V4, 256)), dim3(256), 0, st, canon, g64, g32, g,
+                     antiperiodic(g) ? 1 : 0);
   MG_LAUNCH_CHECK();
 }
 

@@ -1691,6 +1691,265 @@ __global__ __launch_bounds__(TX * TY * TZ * 8, TX * TY * TZ >= 64 ? 1 : 2) void 
   }
 }
 
+// ---------------------------------------------------------------- t-march with LDS exchange (FP64)
+// k_dslash_tx in FP64: one thread per (site, s) of a TX x TY x TZ tile, which
+// walks a chunk of t-slices.  The slice's spinors and links sit in LDS (links of
+// the next slice copied there by global_load_lds meanwhile), so x, y, z
+// neighbours inside the tile and both s neighbours are LDS reads; only face
+// neighbours and slice t + 1 are loaded.  CANON: fields in the canonical order
+// (the 12 components of a site together, 192 bytes per lane).
+// Bound by L2 reads and load latency (two wavefronts per SIMD, 256 VGPRs).
+// 16^3x32x16: 281 us for one field and 3.17 ms for 12 (3.1 TB/s), 4.36 ms for 12
+// canonical ones, against 405 us, 4.85 ms and 6.65 ms with k_dslash, which loads
+// every neighbour and link per lane.  A 4 x 2 x 2 tile with two workgroups per
+// CU: 278 us, 3.35 ms, 4.91 ms.
+typedef double nd2 __attribute__((ext_vector_type(2)));
+typedef const nd2 __attribute__((address_space(1)))* gd2_t;
+typedef nd2 __attribute__((address_space(1)))* gd2w_t;
+typedef const nd2 __attribute__((address_space(3)))* lds_d2_t;
+typedef nd2 __attribute__((address_space(3)))* lds_d2w_t;
+
+template <int TX, int TY, int TZ>
+__device__ __forceinline__ void stage_links_async64(double2* sU, const double2* __restrict__ gp, const DslashArgs& a,
+                                                    long long V4, int tb, int bx, int by, int bz) {
+  constexpr int NS = TX * TY * TZ;
+  constexpr int NF0 = TY * TZ, NF1 = TX * TZ, NF2 = TX * TY;
+  constexpr int NL = 36 * NS + 9 * (NF0 + NF1 + NF2);
+  const int Lx = a.L[0], Ly = a.L[1], Lz = a.L[2];
+  const int lane = (int)threadIdx.x & 63;
+  const int w0 = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), nw = (int)blockDim.x >> 6;
+  for (int g0 = w0 * 64; g0 < NL; g0 += nw * 64) {
+    const int u = g0 + lane;
+    if (u < NL) {
+      int mab, xx, yy, zz;
+      if (u < 36 * NS) {
+        mab = u / NS;
+        const int q = u - mab * NS;
+        xx = bx + q % TX; yy = by + (q / TX) % TY; zz = bz + q / (TX * TY);
+      } else {
+        const int r = u - 36 * NS;
+        if (r < 9 * NF0) {
+          const int ab = r / NF0, f = r - ab * NF0;
+          mab = ab; xx = bx == 0 ? Lx - 1 : bx - 1; yy = by + f % TY; zz = bz + f / TY;
+        } else if (r < 9 * (NF0 + NF1)) {
+          const int r1 = r - 9 * NF0, ab = r1 / NF1, f = r1 - ab * NF1;
+          mab = 9 + ab; xx = bx + f % TX; yy = by == 0 ? Ly - 1 : by - 1; zz = bz + f / TX;
+        } else {
+          const int r2 = r - 9 * (NF0 + NF1), ab = r2 / NF2, f = r2 - ab * NF2;
+          mab = 18 + ab; xx = bx + f % TX; yy = by + f / TX; zz = bz == 0 ? Lz - 1 : bz - 1;
+        }
+      }
+      __builtin_amdgcn_global_load_lds((const void*)(gp + (long long)mab * V4 + tb + (zz * Ly + yy) * Lx + xx),
+                                       (lds_void_t)(void*)(sU + g0), 16, 0, 0);
+    }
+  }
+}
+
+__device__ __forceinline__ void pin_acc64(Spinor<double2>& a) {  // as pin_acc
+#pragma unroll
+  for (int k = 0; k < 12; ++k) {
+    double& re = a.v[k / 3][k % 3].x;
+    double& im = a.v[k / 3][k % 3].y;
+    asm volatile("" : "+v"(re), "+v"(im));
+  }
+}
+
+// spinor at 5D site i5 of the field at base (cs: component stride in bytes)
+template <bool CANON>
+__device__ __forceinline__ unsigned off64(int i5) { return (unsigned)i5 * (CANON ? 192u : 16u); }
+template <bool CANON>
+__device__ __forceinline__ void load_o64(Spinor<double2>& p, const char* base, long long cs, unsigned off) {
+#pragma unroll
+  for (int k = 0; k < 12; ++k) {
+    const nd2 v = *(gd2_t)(sbase(base, CANON ? 16 : cs, k) + off);
+    p.v[k / 3][k % 3] = make_double2(v.x, v.y);
+  }
+}
+
+template <int MU, int EPS, bool DAGU, bool CANON>
+__device__ __forceinline__ void hop_x64(Spinor<double2>& acc, bool inside, lds_d2_t sp, int cst, const char* inb,
+                                        long long cs, unsigned off, lds_d2_t Ul, int ustride) {
+  Spinor<double2> q;
+  double2 U[3][3], h[2][3], u[2][3];
+  if (inside) {
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+      const nd2 v = sp[k * cst];
+      q.v[k / 3][k % 3] = make_double2(v.x, v.y);
+    }
+  } else {
+    load_o64<CANON>(q, inb, cs, off);
+  }
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    const nd2 v = Ul[k * ustride];
+    U[k / 3][k % 3] = make_double2(v.x, v.y);
+  }
+  project<MU, EPS>(q, h);
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      double2 s = make_double2(0.0, 0.0);
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        if (DAGU) cfmac(s, U[j][i], h[r][j]);
+        else cfma(s, U[i][j], h[r][j]);
+      }
+      u[r][i] = s;
+    }
+  accumulate<MU, EPS>(acc, u);
+  pin_acc64(acc);
+}
+
+template <bool CANON, bool DAG, int MODE, int TX, int TY, int TZ>
+__global__ __launch_bounds__(TX * TY * TZ * 16, 2) void k_dslash_dx(const double2* __restrict__ in,
+                                                                   double2* __restrict__ out,
+                                                                   const double2* __restrict__ b,
+                                                                   const double2* __restrict__ gp, TMArgs ta,
+                                                                   double* __restrict__ partial) {
+  constexpr int NS = TX * TY * TZ;
+  constexpr int NF0 = TY * TZ, NF1 = TX * TZ, NF2 = TX * TY;
+  constexpr int NL = 36 * NS + 9 * (NF0 + NF1 + NF2);
+  __shared__ __align__(16) double2 sP[12 * NS * 16];  // slice t: [component][site][s], Ls <= 16
+  __shared__ __align__(16) double2 sU[2][(NL + 63) / 64 * 64];  // own links [mu * 9 + ab][site], then the minus faces
+  const DslashArgs& a = ta.d;
+  const int ntiles = ta.ntx * ta.nty * ta.ntz;
+  int chunk, tile, rhs, pidx;
+  if (ta.fold == 2) {  // XCD units of (right-hand side, z-slab), as in k_dslash_tx
+    const int S = ntiles / ta.zs;
+    const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+    const int u = xcd + 8 * (j / S);
+    rhs = u / ta.zs;
+    tile = (u - rhs * ta.zs) * S + j % S;
+    chunk = 0;
+    pidx = rhs * ntiles + tile;
+  } else {
+    const int bid = xcd_remap(blockIdx.x, gridDim.x);
+    chunk = bid / ntiles;
+    tile = bid - chunk * ntiles;
+    rhs = blockIdx.y;
+    pidx = blockIdx.y * gridDim.x + blockIdx.x;
+  }
+  const int tx = tile % ta.ntx, ty = (tile / ta.ntx) % ta.nty, tz = tile / (ta.ntx * ta.nty);
+  const int Ls = a.Ls;
+  const int site = threadIdx.x / Ls, s = threadIdx.x - site * Ls;
+  const int lc[3] = {site % TX, (site / TX) % TY, site / (TX * TY)};
+  const int x = tx * TX + lc[0], y = ty * TY + lc[1], z = tz * TZ + lc[2];
+  const int Lx = a.L[0], Ly = a.L[1], Lz = a.L[2], Lt = a.L[3];
+  const long long V5 = a.V5, V4 = a.V4;
+  const int V3 = Lx * Ly * Lz;
+  const long long roff = (long long)rhs * 12 * V5;
+  const char* inb = reinterpret_cast<const char*>(in + roff);
+  const char* outb = reinterpret_cast<const char*>(out + roff);
+  const char* bb0 = MODE == 1 ? reinterpret_cast<const char*>(b + roff) : nullptr;
+  const long long cs = V5 * (long long)sizeof(double2);
+  const int x3 = (z * Ly + y) * Lx + x;
+  constexpr int TS[3] = {1, TX, TX * TY};
+  constexpr int TE[3] = {TX, TY, TZ};
+  const int cst = NS * Ls, me = threadIdx.x;
+  int nf3[3], nb3[3], sf[3], sb3[3], lf[3], lb[3], ub[3];
+  bool inF[3], inB[3];
+  {
+    const int co[3] = {x, y, z};
+    const int Lm[3] = {Lx, Ly, Lz};
+    const int st[3] = {1, Lx, Lx * Ly};
+    const int fo[3] = {36 * NS, 36 * NS + 9 * NF0, 36 * NS + 9 * (NF0 + NF1)};
+    const int fi[3] = {lc[1] + TY * lc[2], lc[0] + TX * lc[2], lc[0] + TX * lc[1]};
+    const int nfc[3] = {NF0, NF1, NF2};
+#pragma unroll
+    for (int mu = 0; mu < 3; ++mu) {
+      const bool top = co[mu] == Lm[mu] - 1, bot = co[mu] == 0;
+      nf3[mu] = top ? x3 - (Lm[mu] - 1) * st[mu] : x3 + st[mu];
+      nb3[mu] = bot ? x3 + (Lm[mu] - 1) * st[mu] : x3 - st[mu];
+      inF[mu] = lc[mu] + 1 < TE[mu];
+      inB[mu] = lc[mu] > 0;
+      sf[mu] = inF[mu] ? me + TS[mu] * Ls : me;
+      sb3[mu] = inB[mu] ? me - TS[mu] * Ls : me;
+      lf[mu] = mu * 9 * NS + site;
+      if (inB[mu]) { lb[mu] = mu * 9 * NS + site - TS[mu]; ub[mu] = NS; }
+      else { lb[mu] = fo[mu] + fi[mu]; ub[mu] = nfc[mu]; }
+    }
+  }
+  const int jm = site * Ls + (s == 0 ? Ls - 1 : s - 1), jq = site * Ls + (s == Ls - 1 ? 0 : s + 1);
+  const lds_d2_t lP = (lds_d2_t)(void*)sP;
+  constexpr int EF = DAG ? 1 : -1;
+  constexpr int EB = DAG ? -1 : 1;
+  constexpr int up0 = DAG ? 0 : 2;  // spins coupled to s+1; the others to s-1
+  const double dg = a.diag, cup = s == Ls - 1 ? a.mf : -1.0, cdn = s == 0 ? a.mf : -1.0;
+  const int t0 = chunk * ta.tc;
+  const int t1 = min(t0 + ta.tc, Lt);
+  const int bx = tx * TX, by = ty * TY, bz = tz * TZ;
+  double2 hp[2][3], U[3][3], h[2][3], u[2][3];
+  Spinor<double2> p, acc;
+  {  // half spinor of slice t0 - 1 for the backward t-hop, its link, slice t0
+    const int tm = t0 == 0 ? Lt - 1 : t0 - 1;
+    load_o64<CANON>(p, inb, cs, off64<CANON>((tm * V3 + x3) * Ls + s));
+    project<3, EB>(p, hp);
+    load_link(gp, 3, V4, tm * V3 + x3, U);
+    stage_links_async64<TX, TY, TZ>(sU[t0 & 1], gp, a, V4, t0 * V3, bx, by, bz);
+    load_o64<CANON>(p, inb, cs, off64<CANON>((t0 * V3 + x3) * Ls + s));
+  }
+  double nrm = 0.0;
+  for (int t = t0; t < t1; ++t) {
+    const int tb = t * V3, x4 = tb + x3;
+    __builtin_amdgcn_s_waitcnt(0);  // this wavefront's copies of slice t's links have landed
+    __syncthreads();                // every thread is done with the previous slice's LDS
+    const lds_d2_t lU = (lds_d2_t)(void*)sU[t & 1];
+#pragma unroll
+    for (int k = 0; k < 12; ++k)
+      ((lds_d2w_t)(void*)sP)[k * cst + me] = nd2{p.v[k / 3][k % 3].x, p.v[k / 3][k % 3].y};
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the slice is written; nothing else needs to land
+    __builtin_amdgcn_s_barrier();
+    // own terms (scaled by -2: the sum is halved at the end), backward t-hop
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+      const bool up = k / 3 == up0 || k / 3 == up0 + 1;
+      const nd2 v = lP[k * cst + (up ? jq : jm)];
+      double2 r = cscale(p.v[k / 3][k % 3], dg);
+      r = cadd(r, cscale(make_double2(v.x, v.y), up ? cup : cdn));
+      acc.v[k / 3][k % 3] = cscale(r, -2.0);
+    }
+    mul_link<true>(U, hp, u, 1.0f);
+    accumulate<3, EB>(acc, u);
+    project<3, EB>(p, hp);
+    hop_x64<0, EF, false, CANON>(acc, inF[0], lP + sf[0], cst, inb, cs, off64<CANON>((tb + nf3[0]) * Ls + s), lU + lf[0], NS);
+    hop_x64<0, EB, true, CANON>(acc, inB[0], lP + sb3[0], cst, inb, cs, off64<CANON>((tb + nb3[0]) * Ls + s), lU + lb[0], ub[0]);
+    hop_x64<1, EF, false, CANON>(acc, inF[1], lP + sf[1], cst, inb, cs, off64<CANON>((tb + nf3[1]) * Ls + s), lU + lf[1], NS);
+    hop_x64<1, EB, true, CANON>(acc, inB[1], lP + sb3[1], cst, inb, cs, off64<CANON>((tb + nb3[1]) * Ls + s), lU + lb[1], ub[1]);
+    hop_x64<2, EF, false, CANON>(acc, inF[2], lP + sf[2], cst, inb, cs, off64<CANON>((tb + nf3[2]) * Ls + s), lU + lf[2], NS);
+    hop_x64<2, EB, true, CANON>(acc, inB[2], lP + sb3[2], cst, inb, cs, off64<CANON>((tb + nb3[2]) * Ls + s), lU + lb[2], ub[2]);
+    // forward t-hop with slice t + 1 (its own slice next); the link is the next backward t-hop's
+    const bool top = t == Lt - 1;
+    load_o64<CANON>(p, inb, cs, off64<CANON>(((top ? 0 : t + 1) * V3 + x3) * Ls + s));
+    if (t + 1 < t1) stage_links_async64<TX, TY, TZ>(sU[(t + 1) & 1], gp, a, V4, tb + V3, bx, by, bz);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      const nd2 v = lU[(27 + k) * NS + site];
+      U[k / 3][k % 3] = make_double2(v.x, v.y);
+    }
+    project<3, EF>(p, h);
+    mul_link<false>(U, h, u, 1.0f);
+    accumulate<3, EF>(acc, u);
+    const unsigned o5 = off64<CANON>(x4 * Ls + s);
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+      double2 r = cscale(acc.v[k / 3][k % 3], -0.5);
+      if (MODE == 1) {
+        const nd2 bb = __builtin_nontemporal_load((gd2_t)(sbase(bb0, cs, k) + o5));
+        r = make_double2(bb.x - r.x, bb.y - r.y);
+      }
+      if (CANON) *(gd2w_t)(sbase(outb, 16, k) + o5) = nd2{r.x, r.y};
+      else __builtin_nontemporal_store(nd2{r.x, r.y}, (gd2w_t)(sbase(outb, cs, k) + o5));
+      if (partial) nrm += r.x * r.x + r.y * r.y;
+    }
+  }
+  if (partial) {
+    const double sum = block_sum_dyn(nrm);
+    if (threadIdx.x == 0) partial[pidx] = sum;
+  }
+}
+
 // ---------------------------------------------------------------- t-march, software-pipelined (FP32)
 // k_dslash_tq computes each hop right after loading it, so every hop waits
 // out a full memory round trip: with one wavefront per SIMD nothing else hides
@@ -2165,9 +2424,54 @@ static void launch_ws(const double2*, double2*, const double2*, const double2*, 
   fail(MGDWF_ERR_INVALID_ARG, "the wavefront-per-site-pair kernel is FP32 only");
 }
 
+// Where k_dslash_dx runs: its 4 x 4 x 2 tile divides the lattice, a workgroup
+// has 7 or 8 wavefronts (Ls 14 or 16; the LDS of a CU holds one workgroup) and
+// there are sites enough to fill the chip several slices deep.  Elsewhere
+// k_dslash is as fast or faster (FP64, k_dslash against k_dslash_dx): Ls = 12 on
+// 12^3x24, 4 fields, 304 against 345 us; 8^3x16x16, 4 fields (5.2e5 sites), 62
+// against 70 us.
+constexpr int DXX = 4, DXY = 4, DXZ = 2;
+constexpr long long kDxSites = 1 << 20;
+static bool use_dx(const Geometry& g, int nrhs, bool canon) {
+  return g.L[0] % DXX == 0 && g.L[1] % DXY == 0 && g.L[2] % DXZ == 0 && (g.Ls == 14 || g.Ls == 16) &&
+         (long long)g.V5 * nrhs >= kDxSites && (long long)g.V5 * (canon ? 192 : 16) < (1LL << 32);  // 32-bit lane offsets
+}
+// t-slices per workgroup: one workgroup per CU (a chunk's first slice costs two
+// loads of it; 16^3x32x16, one field: 281 us with 256 workgroups, 298 with 512)
+static TMArgs dx_args(const Geometry& g, int nrhs, const DslashArgs& a) {
+  TMArgs ta;
+  ta.d = a;
+  ta.ntx = g.L[0] / DXX; ta.nty = g.L[1] / DXY; ta.ntz = g.L[2] / DXZ;
+  const long long ntiles = (long long)ta.ntx * ta.nty * ta.ntz;
+  const int want = std::max(1, std::min(g.L[3], ceil_div(256, ntiles * nrhs)));
+  ta.tc = ceil_div(g.L[3], want);
+  ta.nrhs = nrhs;
+  ta.fold = 2;
+  ta.zs = xcd_units_zs(ta.ntz, nrhs);
+  if (ta.zs == 0 || ta.tc < g.L[3]) { ta.fold = 0; ta.zs = 1; }
+  return ta;
+}
+template <bool CANON>
+static void launch_dx(const double2* in, double2* out, const double2* b, const double2* gauge, const Geometry& g,
+                      const TMArgs& ta, bool dagger, int mode, int nrhs, double* partial, hipStream_t st) {
+  const int nb = ta.ntx * ta.nty * ta.ntz * ceil_div(g.L[3], ta.tc);
+  const dim3 grid = ta.fold ? dim3(nb * nrhs, 1) : dim3(nb, nrhs), blk(DXX * DXY * DXZ * g.Ls);
+  const double2* gp = antiperiodic(g) ? gauge + 36LL * g.V4 : gauge;
+#define MG_DX(DAG, MODE) \
+  hipLaunchKernelGGL((k_dslash_dx<CANON, DAG, MODE, DXX, DXY, DXZ>), grid, blk, 0, st, in, out, b, gp, ta, partial)
+  if (!dagger && mode == 0) MG_DX(false, 0);
+  else if (mode == 0) MG_DX(true, 0);
+  else if constexpr (!CANON) {
+    if (!dagger) MG_DX(false, 1);
+    else MG_DX(true, 1);
+  }
+#undef MG_DX
+  MG_LAUNCH_CHECK();
+}
+
 // Kernel choice: FP32 takes the s-pair t-march where the lattice tiles, else the
-// t-march, else the plain kernel; FP64 takes the plain kernel, whose register
-// budget (about 250) keeps two wavefronts per SIMD where the t-march keeps one.
+// t-march, else the plain kernel; FP64 takes k_dslash_dx where use_dx says so,
+// else the plain kernel.
 enum DslashKind { DS_PLAIN, DS_TMARCH, DS_TPAIR };
 
 template <class C2>
@@ -2180,6 +2484,12 @@ static DslashKind dslash_kind(const Geometry& g) {
 
 template <class C2>
 int dslash_nblocks(const Geometry& g, int nrhs) {
+  if constexpr (std::is_same<C2, double2>::value) {
+    if (use_dx(g, nrhs, false)) {
+      const TMArgs ta = dx_args(g, nrhs, DslashArgs{});
+      return ta.ntx * ta.nty * ta.ntz * ceil_div(g.L[3], ta.tc);
+    }
+  }
   switch (dslash_kind<C2>(g)) {
     case DS_TPAIR: {
       const int i = ftile_of(g);
@@ -2200,6 +2510,12 @@ void dslash_ex(const C2* in, C2* out, const C2* b, const C2* gauge, const Geomet
   DslashArgs a;
   for (int m = 0; m < 4; ++m) { a.L[m] = g.L[m]; a.ph[m] = (float)g.bc[m]; }
   a.Ls = g.Ls; a.V4 = g.V4; a.V5 = g.V5; a.diag = 5.0 - M5; a.mf = mf;
+  if constexpr (std::is_same<C2, double2>::value) {
+    if (use_dx(g, nrhs, false)) {
+      launch_dx<false>(in, out, b, gauge, g, dx_args(g, nrhs, a), dagger, mode, nrhs, partial, st);
+      return;
+    }
+  }
   const DslashKind kind = dslash_kind<C2>(g);
   if (kind == DS_TPAIR && kFTiles[ftile_of(g)].ws) {
     const int i = ftile_of(g);
@@ -2270,6 +2586,12 @@ void dslash_canonical(const double2* in, double2* out, const C2* gauge, const Ge
   DslashArgs a;
   for (int m = 0; m < 4; ++m) { a.L[m] = g.L[m]; a.ph[m] = (float)g.bc[m]; }
   a.Ls = g.Ls; a.V4 = g.V4; a.V5 = g.V5; a.diag = 5.0 - M5; a.mf = mf;
+  if constexpr (std::is_same<C2, double2>::value) {
+    if (use_dx(g, nrhs, true)) {
+      launch_dx<true>(in, out, nullptr, gauge, g, dx_args(g, nrhs, a), dagger, 0, nrhs, nullptr, st);
+      return;
+    }
+  }
   const dim3 grid(ceil_div(g.V5, 64), nrhs), blk(256);
   if (dagger)
     hipLaunchKernelGGL((k_dslash<C2, true, true, 0>), grid, blk, 0, st, in, out, nullptr, gauge, a, nullptr);

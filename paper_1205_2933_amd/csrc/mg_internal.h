@@ -39,6 +39,10 @@ struct Geometry {
   int ctile = 0;   // 16-bit coarse apply MFMA shape (0: 16x16x16, 1: 16x16x32)
 };
 
+// Whether some direction is antiperiodic: the FP64 links then have a second,
+// phase-folded copy behind them (else the links themselves are that copy).
+inline bool antiperiodic(const Geometry& g) { return g.bc[0] < 0 || g.bc[1] < 0 || g.bc[2] < 0 || g.bc[3] < 0; }
+
 struct CoarseGeometry {
   int block[4];
   int Lc[4];

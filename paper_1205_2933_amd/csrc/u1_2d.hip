@@ -208,7 +208,7 @@ template void unpack_field<float2>(const mgdwf_ctx*, const float2*, double2*, in
 void pack_gauge_field(mgdwf_ctx* c, const double2* canon) {
   if (c->model == 0) {
     const long long n = 36LL * c->g.V4;
-    c->U64.alloc(n * sizeof(double2));
+    c->U64.alloc((antiperiodic(c->g) ? 2 : 1) * n * sizeof(double2));  // a phase-folded copy where phases exist
     c->U32.alloc(3 * n * sizeof(float2));  // component-major links, a site-major copy, a phase-folded copy
     pack_gauge(canon, c->U64.as<double2>(), c->U32.as<float2>(), c->g, c->st);
     return;

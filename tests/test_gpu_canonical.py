@@ -41,3 +41,53 @@ def test_canonical_and_packed(cuda, L, Ls, n, bc, prec):
             e = float((one - y[k]).norm() / one.norm())
             assert e < TOL[prec], (k, e)
     h.close()
+
+
+@pytest.mark.parametrize("L,Ls,n,bc", [((8, 4, 4, 10), 16, 52, (-1, 1, 1, -1)), ((4, 4, 2, 13), 14, 181, (1, -1, -1, 1))])
+def test_fp64_tile_kernel_against_plain(cuda, L, Ls, n, bc):
+    """Enough fields for the FP64 tile kernel (2^20 sites) against the plain
+    kernel on one field at a time and the oracle: one tile wide in a direction,
+    odd t, antiperiodic faces; canonical fields (apply_dwf)."""
+    import paper_1205_2933_amd as mg
+    U = prepare_gauge(L, 0.4, 83)
+    h = mg.Handle(L, Ls, 1.8, 0.02, bc=bc)
+    mg.mgdwf_set_gauge(h, dev(U))
+    psi = gaussian_fermion(L, Ls, 84, n=n)
+    x = dev(psi)
+    for dagger in (False, True):
+        y = torch.full_like(x, float("nan"))
+        mg.mgdwf_apply_dwf(h, x, y, dagger=dagger, nrhs=n)
+        want = dwf.apply_dwf(psi[n - 1], U, 1.8, 0.02, dagger=dagger, bc=bc)
+        assert np.linalg.norm(y[n - 1].cpu().numpy() - want) / np.linalg.norm(want) < TOL["f64"]
+        for k in range(n):
+            one = torch.empty_like(x[k])
+            mg.mgdwf_apply_dwf(h, x[k].contiguous(), one, dagger=dagger, nrhs=1)
+            assert float((one - y[k]).norm() / one.norm()) < TOL["f64"], k
+    h.close()
+
+
+def test_fp64_tile_kernel_t_chunks(cuda):
+    """One field of 2^20 sites: t in chunks, against the oracle; canonical fields
+    and (CGNE, which stops at once) the residual form on the internal layout."""
+    import paper_1205_2933_amd as mg
+    L, Ls, bc = (8, 16, 8, 64), 16, (1, 1, 1, -1)
+    U = prepare_gauge(L, 0.4, 85)
+    h = mg.Handle(L, Ls, 1.8, 0.02, bc=bc)
+    mg.mgdwf_set_gauge(h, dev(U))
+    psi = gaussian_fermion(L, Ls, 86)
+    x = dev(psi)
+    y = torch.empty_like(x)
+    mg.mgdwf_apply_dwf(h, x, y, nrhs=1)
+    want = dwf.apply_dwf(psi, U, 1.8, 0.02, bc=bc)
+    assert np.linalg.norm(y.cpu().numpy() - want) / np.linalg.norm(want) < TOL["f64"]
+    z = torch.empty_like(x)
+    mg.mgdwf_apply_dwf(h, x, z, dagger=True, nrhs=1)
+    # <D x, y> = <x, D^+ y> with y = D x, and D^+ x through D: <x, D x> = <D^+ x, x>
+    a = torch.vdot(x.reshape(-1), y.reshape(-1))
+    b = torch.vdot(z.reshape(-1), x.reshape(-1))
+    assert abs(complex(a - b)) < 1e-12 * float(x.norm() * y.norm())
+    sol = x.clone()
+    rep = mg.mgdwf_cgne(h, y, sol, tol=1e-12)  # x solves D x = y: residual at rounding on entry
+    assert rep["outer_iters"] == 0 and torch.equal(sol, x)
+    assert rep["true_relres"] < 1e-13
+    h.close()

@@ -164,10 +164,11 @@ void build_coarse_squared(mgdwf_ctx* c) {
     c->have_coarse = true;
     return;
   }
+  const int nb = coarse_build_columns(c->g);
   double2* work9 = c->buf<double2>("dc_work9", 9 * field);
-  double2* zwork9 = c->buf<double2>("dc_zwork9", 9 * field);
-  double2* cwork = c->buf<double2>("dc_cwork", 9LL * cg.Vc * cg.n2);
-  double* partial = c->buf<double>("dc_partial", restrict_partial_doubles(cg, 9));
+  double2* zwork9 = c->buf<double2>("dc_zwork9", 9 * nb * field);
+  double2* cwork = c->buf<double2>("dc_cwork", 9LL * nb * cg.Vc * cg.n2);
+  double* partial = c->buf<double>("dc_partial", restrict_partial_doubles(cg, 9 * nb));
   build_sq_coarse_op(c->V64.as<double2>(), c->U64.as<double2>(), c->Asq.m64.as<double2>(), work9, zwork9, cwork,
                      partial, c->g, cg, c->M5, c->mf, c->st);
   c->Asq.m32.alloc(sq_coarse_entries(cg) * sizeof(float2));
@@ -186,9 +187,10 @@ void build_coarse(mgdwf_ctx* c) {
   const CoarseGeometry& cg = c->cg;
   const long long ndc = (long long)cg.Vc * 9 * cg.n2 * cg.n2;
   c->Dc.m64.alloc(ndc * sizeof(double2));
-  double2* work9 = c->buf<double2>("dc_work9", 9 * c->fine_len());
-  double2* cwork = c->buf<double2>("dc_cwork", 9LL * cg.Vc * cg.n2);
-  double* partial = c->buf<double>("dc_partial", restrict_partial_doubles(cg, 9));
+  const int nb = coarse_build_columns(c->g);
+  double2* work9 = c->buf<double2>("dc_work9", 9 * nb * c->fine_len());
+  double2* cwork = c->buf<double2>("dc_cwork", 9LL * nb * cg.Vc * cg.n2);
+  double* partial = c->buf<double>("dc_partial", restrict_partial_doubles(cg, 9 * nb));
   build_coarse_op(c->V64.as<double2>(), c->U64.as<double2>(), c->Dc.m64.as<double2>(), work9, cwork, partial, c->g,
                   cg, c->M5, c->mf, c->st);
   finish_coarse_op(c->Dc, c->DcH, cg, c->st);

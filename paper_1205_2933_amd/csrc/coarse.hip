@@ -38,17 +38,17 @@ void dslash_split(const double2* in, double2* out9, const double2* gauge, const 
 
 namespace {
 
-// Dc column j for all (X, d): coarse[d][X][row] (from the restriction of field d)
-// -> Dc[((X*9 + d)*n2 + j)*n2 + row].
-__global__ void k_scatter_column(const double2* __restrict__ coarse, double2* __restrict__ Dc, int Vc,
-                                 int n2, int j) {
+// Dc columns j0 .. j0 + nb - 1 for all (X, d): coarse[j - j0][d][X][row] (from the
+// restriction of field d) -> Dc[((X*9 + d)*n2 + j)*n2 + row].
+__global__ void k_scatter_columns(const double2* __restrict__ coarse, double2* __restrict__ Dc, int Vc,
+                                  int n2, int j0, int nb) {
   long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  long long tot = 9LL * Vc * n2;
+  long long tot = 9LL * Vc * n2 * nb;
   if (i >= tot) return;
   int row = (int)(i % n2);
   long long t = i / n2;
-  int X = (int)(t % Vc), d = (int)(t / Vc);
-  Dc[(((long long)X * 9 + d) * n2 + j) * n2 + row] = coarse[i];
+  int X = (int)(t % Vc), dj = (int)(t / Vc);
+  Dc[(((long long)X * 9 + dj % 9) * n2 + j0 + dj / 9) * n2 + row] = coarse[i];
 }
 
 struct CoarseArgs {
@@ -766,23 +766,29 @@ __global__ __launch_bounds__(576) void k_cgne_persistent(PersistArgs q) {
 
 }  // namespace
 
+// Columns of a coarse build restricted together: the restriction reads the basis
+// once per 32 right-hand sides, three columns' nine pieces fill 27; one column
+// at a time where 27 FP64 fields would pass 16 GB.
+int coarse_build_columns(const Geometry& g) { return 27.0 * 12 * 16 * g.V5 <= 16e9 ? 3 : 1; }
+
 // Build the FP64 coarse operator.  Vhat: orthonormal basis (Nv FP64 fields);
-// work9: 9 fine FP64 fields; cwork: 9 * Vc * n2 complex; partial: restriction
-// scratch for 9 right-hand sides.
+// with nb = coarse_build_columns: work9: 9 nb fine FP64 fields; cwork: 9 nb Vc n2
+// complex; partial: restriction scratch for 9 nb right-hand sides.
 void build_coarse_op(const double2* Vhat, const double2* gauge, double2* Dc, double2* work9, double2* cwork,
                      double* partial, const Geometry& g, const CoarseGeometry& cg, double M5, double mf,
                      hipStream_t st) {
   const long long field = 12LL * g.V5;
-  for (int chi = 0; chi < 2; ++chi)
-    for (int k = 0; k < cg.Nv; ++k) {
-      dslash_split(Vhat + k * field, work9, gauge, g, cg.block, M5, mf, chi, st);
-      restrict_op<double2, double2>(Vhat, work9, cwork, partial, g, cg, 9, st);
-      const int j = chi * cg.Nv + k;
-      long long tot = 9LL * cg.Vc * cg.n2;
-      hipLaunchKernelGGL(k_scatter_column, dim3(ceil_div(tot, 256)), dim3(256), 0, st, cwork, Dc, cg.Vc,
-                         cg.n2, j);
-      MG_LAUNCH_CHECK();
-    }
+  const int nbmax = coarse_build_columns(g);
+  for (int j0 = 0; j0 < cg.n2; j0 += nbmax) {
+    const int nb = std::min(nbmax, cg.n2 - j0);
+    for (int q = 0; q < nb; ++q)  // column j = chi * Nv + k
+      dslash_split(Vhat + (j0 + q) % cg.Nv * field, work9 + q * 9 * field, gauge, g, cg.block, M5, mf,
+                   (j0 + q) / cg.Nv, st);
+    restrict_op<double2, double2>(Vhat, work9, cwork, partial, g, cg, 9 * nb, st);
+    long long tot = 9LL * cg.Vc * cg.n2 * nb;
+    hipLaunchKernelGGL(k_scatter_columns, dim3(ceil_div(tot, 256)), dim3(256), 0, st, cwork, Dc, cg.Vc, cg.n2, j0, nb);
+    MG_LAUNCH_CHECK();
+  }
 }
 
 static void pack_store(CoarseStore& s, const CoarseGeometry& cg, hipStream_t st) {

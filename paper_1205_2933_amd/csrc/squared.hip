@@ -217,8 +217,9 @@ __global__ void k_sq_canonical(const double2* __restrict__ in, double2* __restri
 
 size_t sq_coarse_entries(const CoarseGeometry& cg) { return (size_t)cg.Vc * 33 * cg.n2 * cg.n2; }
 
-// Build A_c (FP64) into Ac; work9 and zwork9: 9 fine FP64 fields each; cwork:
-// 9 Vc n2 complex; partial: restriction scratch for 9 right-hand sides.
+// Build A_c (FP64) into Ac; with nb = coarse_build_columns: work9: 9 fine FP64
+// fields, zwork9: 9 nb; cwork: 9 nb Vc n2 complex; partial: restriction scratch
+// for 9 nb right-hand sides.
 void build_sq_coarse_op(const double2* Vhat, const double2* gauge, double2* Ac, double2* work9, double2* zwork9,
                         double2* cwork, double* partial, const Geometry& g, const CoarseGeometry& cg, double M5,
                         double mf, hipStream_t st) {
@@ -228,23 +229,24 @@ void build_sq_coarse_op(const double2* Vhat, const double2* gauge, double2* Ac, 
   MG_LAUNCH_CHECK();
   int off[33][4];
   offset_table(off);
+  const int nb = coarse_build_columns(g);
+  const long long nc9 = 9LL * cg.Vc * cg.n2;
   for (int chi = 0; chi < 2; ++chi)
     for (int k = 0; k < cg.Nv; ++k) {
       const int j = chi * cg.Nv + k;
       dslash_split(Vhat + k * field, work9, gauge, g, cg.block, M5, mf, chi, st, false);  // W_e, e = 0..8
-      for (int e = 0; e < 9; ++e) {
-        PairIdx pi;
-        bool any = false;
-        for (int d = 0; d < 9; ++d) {
-          pi.oi[d] = pair_offset(off, d, e);
-          any = any || pi.oi[d] >= 0;
+      for (int e0 = 0; e0 < 9; e0 += nb) {  // nb pieces' nine fields restricted together
+        const int ne = std::min(nb, 9 - e0);
+        for (int q = 0; q < ne; ++q)
+          dslash_split(work9 + (e0 + q) * field, zwork9 + q * 9 * field, gauge, g, cg.block, M5, mf, -1, st, true);
+        restrict_op<double2, double2>(Vhat, zwork9, cwork, partial, g, cg, 9 * ne, st);
+        for (int q = 0; q < ne; ++q) {  // one after the other: two pieces may add to the same entry
+          PairIdx pi;
+          for (int d = 0; d < 9; ++d) pi.oi[d] = pair_offset(off, d, e0 + q);
+          hipLaunchKernelGGL(k_sq_scatter, dim3(ceil_div(nc9, 256)), dim3(256), 0, st, cwork + q * nc9, Ac, cg.Vc, cg.n2,
+                             j, pi);
+          MG_LAUNCH_CHECK();
         }
-        if (!any) continue;
-        dslash_split(work9 + (long long)e * field, zwork9, gauge, g, cg.block, M5, mf, -1, st, true);
-        restrict_op<double2, double2>(Vhat, zwork9, cwork, partial, g, cg, 9, st);
-        const long long tot = 9LL * cg.Vc * cg.n2;
-        hipLaunchKernelGGL(k_sq_scatter, dim3(ceil_div(tot, 256)), dim3(256), 0, st, cwork, Ac, cg.Vc, cg.n2, j, pi);
-        MG_LAUNCH_CHECK();
       }
     }
 }

@@ -77,6 +77,7 @@ void prolong_op(const C2* V, const CC2* coarse, C2* fine, bool accumulate, const
 bool orthonormalise_basis(double2* V, const Geometry& g, const CoarseGeometry& cg, hipStream_t st);
 
 // coarse.hip
+int coarse_build_columns(const Geometry& g);  // columns built together (sizes the builds' workspaces)
 void build_coarse_op(const double2* Vhat, const double2* gauge, double2* Dc, double2* work9, double2* cwork,
                      double* partial, const Geometry& g, const CoarseGeometry& cg, double M5, double mf,
                      hipStream_t st);

@@ -28,10 +28,6 @@
 
 namespace mgdwf {
 
-// from transfer.hip
-template <class C2, class CC2>
-void restrict_op(const C2* V, const C2* x, CC2* coarse, double* partial, const Geometry& g,
-                 const CoarseGeometry& cg, int nrhs, hipStream_t st);
 // from dslash.hip
 void dslash_split(const double2* in, double2* out9, const double2* gauge, const Geometry& g, const int block[4],
                   double M5, double mf, int chi, hipStream_t st, bool dagger = false);
@@ -258,14 +254,14 @@ template <int N2> __host__ __device__ constexpr int slab_floats() { return 9 * 1
 
 template <int N2>
 __device__ __forceinline__ float2 slab_sum(const float* slab, int col, int row) {
-  float2 s = make_float2(0.f, 0.f);
+  double re = 0.0, im = 0.0;  // FP64: the sum over directions adds no rounding of its own
 #pragma unroll
   for (int d = 0; d < 9; ++d) {
     const float* q = slab + (d * 16 + col) * slab_stride<N2>() + row;
-    s.x += q[0];
-    s.y += q[N2];
+    re += q[0];
+    im += q[N2];
   }
-  return s;
+  return make_float2((float)re, (float)im);
 }
 
 template <int N2>

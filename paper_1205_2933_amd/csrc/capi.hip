@@ -83,6 +83,7 @@ CoarseGeometry make_coarse(const mgdwf_ctx* c, const int32_t block[4], int nvec)
        "nvec exceeds the block's dof per chirality");
   cg.Nv = nvec;
   cg.n2 = 2 * nvec;
+  cg.planar = c->model == 1;
   return cg;
 }
 
@@ -164,11 +165,10 @@ void build_coarse_squared(mgdwf_ctx* c) {
     c->have_coarse = true;
     return;
   }
-  const int nb = coarse_build_columns(c->g);
   double2* work9 = c->buf<double2>("dc_work9", 9 * field);
-  double2* zwork9 = c->buf<double2>("dc_zwork9", 9 * nb * field);
-  double2* cwork = c->buf<double2>("dc_cwork", 9LL * nb * cg.Vc * cg.n2);
-  double* partial = c->buf<double>("dc_partial", restrict_partial_doubles(cg, 9 * nb));
+  double2* zwork9 = c->buf<double2>("dc_zwork9", 9 * field);
+  double2* cwork = c->buf<double2>("dc_cwork", 9LL * cg.Vc * cg.n2);
+  double* partial = c->buf<double>("dc_partial", restrict_partial_doubles(cg, 9));
   build_sq_coarse_op(c->V64.as<double2>(), c->U64.as<double2>(), c->Asq.m64.as<double2>(), work9, zwork9, cwork,
                      partial, c->g, cg, c->M5, c->mf, c->st);
   c->Asq.m32.alloc(sq_coarse_entries(cg) * sizeof(float2));
@@ -509,11 +509,9 @@ mgdwf_status mgdwf_apply_coarse(mgdwf_handle h, const double* in, double* out, i
         sq_apply64(h->Asq.m64.as<double2>(), reinterpret_cast<const double2*>(in), reinterpret_cast<double2*>(out),
                    h->cg, nrhs, h->st);
       } else {
-        float2* a = h->buf<float2>("cio_a32", n);
-        float2* b = h->buf<float2>("cio_b32", n);
+        float2* a = h->buf<float2>("cio_a32", n);  // a copy, so in and out may be one buffer
         convert<double2, float2>(reinterpret_cast<const double2*>(in), a, n, h->st);
-        sq_apply32(h->Asq.m32.as<float2>(), a, b, h->cg, nrhs, h->st);
-        convert<float2, double2>(b, reinterpret_cast<double2*>(out), n, h->st);
+        sq_apply32(h->Asq.m32.as<float2>(), a, reinterpret_cast<double2*>(out), h->cg, nrhs, h->st);
       }
       return;
     }
@@ -549,7 +547,7 @@ mgdwf_status mgdwf_apply_coarse_noalloc(mgdwf_handle h, const double* in, double
       else coarse_apply64(dagger ? h->DcH : h->Dc, x, y, h->cg, nrhs, h->st);
       return;
     }
-    // scratch: the FP32 input and output, then the 16-bit packed input
+    // scratch: room for the FP32 input and output, then the 16-bit packed input
     auto up = [](size_t b) { return (b + 255) / 256 * 256; };
     const size_t vec = up((size_t)n * sizeof(float2));
     const size_t pack = (!sq && prec != MGDWF_F32) ? coarse_pack_bytes(h->cg, nrhs) : 0;
@@ -557,11 +555,9 @@ mgdwf_status mgdwf_apply_coarse_noalloc(mgdwf_handle h, const double* in, double
          "coarse vectors too large for the 16 MiB no-allocation scratch (use mgdwf_apply_coarse)");
     char* s = static_cast<char*>(h->scratch);
     float2* a = reinterpret_cast<float2*>(s);
-    float2* b = reinterpret_cast<float2*>(s + vec);
     if (sq) {
       convert<double2, float2>(x, a, n, h->st);
-      sq_apply32(h->Asq.m32.as<float2>(), a, b, h->cg, nrhs, h->st);
-      convert<float2, double2>(b, y, n, h->st);
+      sq_apply32(h->Asq.m32.as<float2>(), a, y, h->cg, nrhs, h->st);
     } else {
       coarse_apply_reduced(h, dagger ? h->DcH : h->Dc, prec, x, y, nrhs, a, s + 2 * vec);
     }
@@ -1028,7 +1024,7 @@ mgdwf_status mgdwf_tune(mgdwf_handle h, int32_t nrhs, int32_t iters, mgdwf_tune_
       if (!dslash_ftile_desc(g, i, nrhs, desc, &flags)) continue;
       auto run = [&](int n) {
         for (int k = 0; k < n; ++k)
-          dslash_ex<float2>(a, b, nullptr, h->U32.as<float2>(), g, h->M5, h->mf, (k & 1) != 0, 0, nrhs, nullptr,
+          dslash_ex<float2>(a, b, nullptr, h->U32.as<float2>(), g, h->M5, h->mf, (k & 1) != 0, 0, nrhs, nullptr, false,
                             h->st);
       };
       run(2);

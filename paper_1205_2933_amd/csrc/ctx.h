@@ -36,6 +36,14 @@ struct mgdwf_ctx {
   mgdwf::CoarseGeometry cg2{};   // level-2 lattice: Lc = blocks, Vc, Nv = Nv2, n2, block = coarse sites per block
   mgdwf::DevBuf W2null, W2_64, W2_32, Acc64, Acc32;
 
+  // Sums in one fixed order that no lattice-dependent kernel choice changes: during
+  // a squared setup (and its builds) and a squared mixed-precision solve (KeepOrder).
+  // Such a solve stops at a residual that leaves 1e-9 to 5e-9 of error in D's lowest
+  // modes, and a single rounding redraws it: with the right-hand sides scaled by 1 +
+  // 1e-15 the solutions move by 9e-10 to 5e-9 and the outer iterations from 96 to 87
+  // (8^3x16x16, m_f 0.001, residual 1e-10).  The 9-point solves move by 1e-10.
+  bool keep_order = false;
+
   mgdwf_mg_params mp{};
   bool have_params = false;
 
@@ -115,6 +123,16 @@ struct mgdwf_ctx {
 
 namespace mgdwf {
 
+// keep_order for a scope
+struct KeepOrder {
+  mgdwf_ctx* c;
+  const bool before;
+  KeepOrder(mgdwf_ctx* ctx, bool on) : c(ctx), before(ctx->keep_order) { c->keep_order = on || before; }
+  ~KeepOrder() { c->keep_order = before; }
+  KeepOrder(const KeepOrder&) = delete;
+  KeepOrder& operator=(const KeepOrder&) = delete;
+};
+
 // Fine-level operations of the handle's model (u1_2d.hip): the 4D kernels for
 // model 0, the 2D ones for model 1.
 template <class F2> void pack_field(const mgdwf_ctx* c, const double2* canon, F2* field, int nrhs);
@@ -123,6 +141,7 @@ template <class F2> void unpack_field(const mgdwf_ctx* c, const F2* field, doubl
 void pack_gauge_field(mgdwf_ctx* c, const double2* canon);
 // workgroups (partial sums per right-hand side) of fine_dslash with a partial buffer
 template <class F2> int fine_nblocks(const mgdwf_ctx* c, int nrhs);
+template <class F2> int fine_group(const mgdwf_ctx* c, int nrhs);  // of them, added first (finalize_rhs)
 // out = D in (D^+ for dag); mode 1: out = b - D in; partial: per-workgroup |out|^2
 template <class F2>
 void fine_dslash(const mgdwf_ctx* c, const F2* in, F2* out, const F2* b, bool dag, int mode, int nrhs,

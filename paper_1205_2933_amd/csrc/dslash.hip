@@ -149,8 +149,11 @@ struct DslashArgs {
 
 // The plain kernel, for every lattice and both precisions.  A workgroup covers
 // 64 consecutive 5D sites (x4, s); its four wavefronts take the same sites, one
-// direction mu each (both hops), leave their sums in LDS, and then take one
-// spin each for the diagonal, the fifth dimension and the store.
+// direction mu each (both hops), leave the transported half spinors in LDS, and
+// then take one spin each for the hop sum, the diagonal, the fifth dimension and
+// the store.  Every sum runs in the order of a thread that does all of it (hops
+// +x, -x, +y, ..., components in order), which a squared mixed-precision solve
+// relies on (keep_order in ctx.h).
 // Bound by the latency of its one round of loads on small lattices (4^4x8, FP64:
 // 3.9 us, 8.8 with one thread per site and all eight hops in a row), by L2 reads
 // on large ones (16^3x32x16, FP64: 410 us per field, every neighbour and link
@@ -171,13 +174,14 @@ struct FieldIO {
   }
 };
 
-// both hops of direction MU at (x4, s) into acc
+// The transported half spinors of both hops of direction MU at (x4, s) into
+// sm[2 MU] (forward) and sm[2 MU + 1] (backward)
 template <int MU, bool DAG, class C2, bool CANON>
-__device__ __forceinline__ void hops_mu(Spinor<C2>& acc, const typename FieldIO<C2, CANON>::IO* __restrict__ in,
+__device__ __forceinline__ void hops_mu(C2 (*sm)[6][64], const typename FieldIO<C2, CANON>::IO* __restrict__ in,
                                         const C2* __restrict__ gauge, const DslashArgs& a, int x4, int s) {
   constexpr int EF = DAG ? 1 : -1, EB = DAG ? -1 : 1;
   const int st = MU == 0 ? 1 : (MU == 1 ? a.L[0] : (MU == 2 ? a.L[0] * a.L[1] : a.L[0] * a.L[1] * a.L[2]));
-  const int co = (x4 / st) % a.L[MU];
+  const int co = (x4 / st) % a.L[MU], l = threadIdx.x & 63;
   const bool top = co == a.L[MU] - 1, bot = co == 0;
   const int xf = top ? x4 - (a.L[MU] - 1) * st : x4 + st;
   const int xb = bot ? x4 + (a.L[MU] - 1) * st : x4 - st;
@@ -187,31 +191,52 @@ __device__ __forceinline__ void hops_mu(Spinor<C2>& acc, const typename FieldIO<
     pf.v[c / 3][c % 3] = FieldIO<C2, CANON>::get(in, c, a.V5, (long long)xf * a.Ls + s);
     pb.v[c / 3][c % 3] = FieldIO<C2, CANON>::get(in, c, a.V5, (long long)xb * a.Ls + s);
   }
-#pragma unroll
-  for (int c = 0; c < 12; ++c) acc.v[c / 3][c % 3] = cmk<C2>(0, 0);
   C2 h[2][3], u[2][3];
+  const auto leave = [&](int hop, bool face) {
+#pragma unroll
+    for (int c = 0; c < 6; ++c)
+      sm[hop][c][l] = face ? cscale(u[c / 3][c % 3], a.ph[MU]) : u[c / 3][c % 3];
+  };
   project<MU, EF>(pf, h);
   transport<false>(gauge, MU, (long long)a.V4, x4, h, u);
-  if (top && a.ph[MU] != 1.0f) {
-#pragma unroll
-    for (int r = 0; r < 2; ++r)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) u[r][c] = cscale(u[r][c], a.ph[MU]);
-  }
-  accumulate<MU, EF>(acc, u);
+  leave(2 * MU, top);
   project<MU, EB>(pb, h);
   transport<true>(gauge, MU, (long long)a.V4, xb, h, u);
-  if (bot && a.ph[MU] != 1.0f) {
-#pragma unroll
-    for (int r = 0; r < 2; ++r)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) u[r][c] = cscale(u[r][c], a.ph[MU]);
-  }
-  accumulate<MU, EB>(acc, u);
+  leave(2 * MU + 1, bot);
 }
 
-// MODE 0: out = D in;  MODE 1: out = b - D in.  partial (if non-null) gets the
-// per-workgroup sum of |out|^2 at index blockIdx.y * gridDim.x + blockIdx.x.
+// component c of spin W of (1 + EPS g_MU) reconstructed from a half spinor in
+// LDS (accumulate's map)
+template <int MU, int EPS, int W, class C2>
+__device__ __forceinline__ C2 from_half(const C2 (*hs)[64], int c, int l) {
+  constexpr int up = W < 2 ? W : (MU == 0 || MU == 1 ? 3 - W : W - 2);  // which half-spinor row
+  const C2 u = hs[up * 3 + c][l];
+  if (W < 2) return u;
+  const C2 v = MU == 0 || MU == 2 ? ci(u) : u;
+  constexpr int sign = (MU == 1 || MU == 2) && W == 3 ? -EPS : EPS;
+  return cscale(v, (float)sign);
+}
+
+template <bool DAG, int W, class C2>
+__device__ __forceinline__ C2 hop_sum(const C2 (*sm)[6][64], int c, int l) {
+  constexpr int EF = DAG ? 1 : -1, EB = DAG ? -1 : 1;
+  C2 s = cmk<C2>(0, 0);
+  s = cadd(s, from_half<0, EF, W>(sm[0], c, l));
+  s = cadd(s, from_half<0, EB, W>(sm[1], c, l));
+  s = cadd(s, from_half<1, EF, W>(sm[2], c, l));
+  s = cadd(s, from_half<1, EB, W>(sm[3], c, l));
+  s = cadd(s, from_half<2, EF, W>(sm[4], c, l));
+  s = cadd(s, from_half<2, EB, W>(sm[5], c, l));
+  s = cadd(s, from_half<3, EF, W>(sm[6], c, l));
+  s = cadd(s, from_half<3, EB, W>(sm[7], c, l));
+  return s;
+}
+
+// MODE 0: out = D in;  MODE 1: out = b - D in.  The grid has four workgroups per
+// 256 sites; partial (if non-null) gets each one's sum of |out|^2, the four of 256
+// sites next to each other in the order of the 256-site workgroups (index q in
+// xcd_remap's numbering), so that adding four and then the groups gives the sums
+// of 256-thread workgroups.
 template <class C2, bool CANON, bool DAG, int MODE>
 __global__ __launch_bounds__(256) void k_dslash(const typename FieldIO<C2, CANON>::IO* __restrict__ in,
                                                 typename FieldIO<C2, CANON>::IO* __restrict__ out,
@@ -219,10 +244,12 @@ __global__ __launch_bounds__(256) void k_dslash(const typename FieldIO<C2, CANON
                                                 double* __restrict__ partial) {
   using T = typename real_of<C2>::type;
   using IO = FieldIO<C2, CANON>;
-  __shared__ C2 sm[4][12][64];
-  const int bid = xcd_remap(blockIdx.x, gridDim.x);
+  __shared__ C2 sm[8][6][64];
+  // four workgroups of one 256-site group follow each other on one XCD
+  const int n256 = gridDim.x >> 2, j = blockIdx.x, full = n256 / 8 * 32;
+  const int q = j < full ? (j >> 5) * 8 + (j & 7) : j >> 2, sub = j < full ? (j >> 3) & 3 : j & 3;
   const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), l = threadIdx.x & 63;
-  const long long V5 = a.V5, i5 = (long long)bid * 64 + l;
+  const long long V5 = a.V5, i5 = (long long)xcd_remap(q, n256) * 256 + sub * 64 + l;
   const long long roff = (long long)blockIdx.y * 12 * V5;
   in += roff;
   out += roff;
@@ -230,16 +257,13 @@ __global__ __launch_bounds__(256) void k_dslash(const typename FieldIO<C2, CANON
   const int Ls = a.Ls;
   const int x4 = (int)(i5 / Ls), s = (int)(i5 - (long long)x4 * Ls);
   if (i5 < V5) {
-    Spinor<C2> acc;
-    if (w == 0) hops_mu<0, DAG, C2, CANON>(acc, in, gauge, a, x4, s);
-    else if (w == 1) hops_mu<1, DAG, C2, CANON>(acc, in, gauge, a, x4, s);
-    else if (w == 2) hops_mu<2, DAG, C2, CANON>(acc, in, gauge, a, x4, s);
-    else hops_mu<3, DAG, C2, CANON>(acc, in, gauge, a, x4, s);
-#pragma unroll
-    for (int c = 0; c < 12; ++c) sm[w][c][l] = acc.v[c / 3][c % 3];
+    if (w == 0) hops_mu<0, DAG, C2, CANON>(sm, in, gauge, a, x4, s);
+    else if (w == 1) hops_mu<1, DAG, C2, CANON>(sm, in, gauge, a, x4, s);
+    else if (w == 2) hops_mu<2, DAG, C2, CANON>(sm, in, gauge, a, x4, s);
+    else hops_mu<3, DAG, C2, CANON>(sm, in, gauge, a, x4, s);
   }
   __syncthreads();
-  double nrm = 0.0;
+  C2 r[3];
   if (i5 < V5) {
     // spin w: coupled to s + 1 are {2,3} for D, {0,1} for D^+; the others to s - 1
     const bool up = DAG ? w < 2 : w >= 2;
@@ -247,19 +271,32 @@ __global__ __launch_bounds__(256) void k_dslash(const typename FieldIO<C2, CANON
     const int sn = up ? (wall ? 0 : s + 1) : (wall ? Ls - 1 : s - 1);
     const T cn = wall ? (T)a.mf : (T)-1, half = (T)-0.5, dg = (T)a.diag;
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const int c = w * 3 + q;
-      const C2 hop = cadd(cadd(cadd(sm[0][c][l], sm[1][c][l]), sm[2][c][l]), sm[3][c][l]);
-      C2 r = cadd(cscale(IO::get(in, c, V5, i5), dg), cscale(hop, half));
-      r = cadd(r, cscale(IO::get(in, c, V5, (long long)x4 * Ls + sn), cn));
-      if (MODE == 1) r = csub(b[c * V5 + i5], r);
-      IO::put(out, c, V5, i5, r);
-      nrm += (double)r.x * r.x + (double)r.y * r.y;
+    for (int k = 0; k < 3; ++k) {
+      const int c = w * 3 + k;
+      const C2 hop = w == 0 ? hop_sum<DAG, 0>(sm, k, l) : (w == 1 ? hop_sum<DAG, 1>(sm, k, l)
+                     : (w == 2 ? hop_sum<DAG, 2>(sm, k, l) : hop_sum<DAG, 3>(sm, k, l)));
+      r[k] = cadd(cscale(IO::get(in, c, V5, i5), dg), cscale(hop, half));
+      r[k] = cadd(r[k], cscale(IO::get(in, c, V5, (long long)x4 * Ls + sn), cn));
+      if (MODE == 1) r[k] = csub(b[c * V5 + i5], r[k]);
+      IO::put(out, c, V5, i5, r[k]);
     }
   }
-  if (partial) {
-    double sum = block_sum<256>(nrm);
-    if (threadIdx.x == 0) partial[(long long)blockIdx.y * gridDim.x + blockIdx.x] = sum;
+  if (partial) {  // a site's twelve components in order, then the sites
+    __syncthreads();
+    C2 (*res)[64] = reinterpret_cast<C2 (*)[64]>(&sm[0][0][0]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) res[w * 3 + k][l] = i5 < V5 ? r[k] : cmk<C2>(0, 0);
+    __syncthreads();
+    if (w == 0) {
+      double nrm = 0.0;
+#pragma unroll
+      for (int c = 0; c < 12; ++c) {
+        const C2 v = res[c][l];
+        nrm += (double)v.x * v.x + (double)v.y * v.y;
+      }
+      nrm = wave_sum(nrm);
+      if (l == 0) partial[(long long)blockIdx.y * gridDim.x + q * 4 + sub] = nrm;
+    }
   }
 }
 
@@ -2482,10 +2519,20 @@ static DslashKind dslash_kind(const Geometry& g) {
   return DS_PLAIN;
 }
 
+// Partial sums per right-hand side that belong together: the plain kernel leaves
+// four per 256 sites, to be added first.
 template <class C2>
-int dslash_nblocks(const Geometry& g, int nrhs) {
+int dslash_group(const Geometry& g, int nrhs, bool keep_order) {
+  if (std::is_same<C2, double2>::value && !keep_order && use_dx(g, nrhs, false)) return 1;
+  return dslash_kind<C2>(g) == DS_PLAIN ? 4 : 1;
+}
+template int dslash_group<double2>(const Geometry&, int, bool);
+template int dslash_group<float2>(const Geometry&, int, bool);
+
+template <class C2>
+int dslash_nblocks(const Geometry& g, int nrhs, bool keep_order) {
   if constexpr (std::is_same<C2, double2>::value) {
-    if (use_dx(g, nrhs, false)) {
+    if (!keep_order && use_dx(g, nrhs, false)) {
       const TMArgs ta = dx_args(g, nrhs, DslashArgs{});
       return ta.ntx * ta.nty * ta.ntz * ceil_div(g.L[3], ta.tc);
     }
@@ -2498,20 +2545,20 @@ int dslash_nblocks(const Geometry& g, int nrhs) {
     case DS_TMARCH:
       return (g.L[0] / TMX) * (g.L[1] / TMY) * (g.L[2] / TMZ) * ceil_div(g.L[3], tmarch_chunk(g));
     default:
-      return ceil_div(g.V5, 64);
+      return 4 * ceil_div(g.V5, 256);
   }
 }
-template int dslash_nblocks<double2>(const Geometry&, int);
-template int dslash_nblocks<float2>(const Geometry&, int);
+template int dslash_nblocks<double2>(const Geometry&, int, bool);
+template int dslash_nblocks<float2>(const Geometry&, int, bool);
 
 template <class C2>
 void dslash_ex(const C2* in, C2* out, const C2* b, const C2* gauge, const Geometry& g, double M5,
-               double mf, bool dagger, int mode, int nrhs, double* partial, hipStream_t st) {
+               double mf, bool dagger, int mode, int nrhs, double* partial, bool keep_order, hipStream_t st) {
   DslashArgs a;
   for (int m = 0; m < 4; ++m) { a.L[m] = g.L[m]; a.ph[m] = (float)g.bc[m]; }
   a.Ls = g.Ls; a.V4 = g.V4; a.V5 = g.V5; a.diag = 5.0 - M5; a.mf = mf;
   if constexpr (std::is_same<C2, double2>::value) {
-    if (use_dx(g, nrhs, false)) {
+    if (!keep_order && use_dx(g, nrhs, false)) {
       launch_dx<false>(in, out, b, gauge, g, dx_args(g, nrhs, a), dagger, mode, nrhs, partial, st);
       return;
     }
@@ -2547,7 +2594,7 @@ void dslash_ex(const C2* in, C2* out, const C2* b, const C2* gauge, const Geomet
       ta.zs = xcd_units_zs(ta.ntz, nrhs);
       if (ta.zs == 0 || ta.tc < g.L[3]) { ta.fold = 0; ta.zs = 1; }
     }
-    const int nb = dslash_nblocks<C2>(g, nrhs);
+    const int nb = dslash_nblocks<C2>(g, nrhs, keep_order);
     const dim3 grid = ta.fold ? dim3(nb * nrhs, 1) : dim3(nb, nrhs);
     launch_tpair(in, out, b, gauge, ta, partial, dagger, mode, grid, dim3(f.tx * f.ty * f.tz * g.Ls / 2), i, st);
     MG_LAUNCH_CHECK();
@@ -2558,7 +2605,7 @@ void dslash_ex(const C2* in, C2* out, const C2* b, const C2* gauge, const Geomet
     ta.d = a;
     ta.ntx = g.L[0] / TMX; ta.nty = g.L[1] / TMY; ta.ntz = g.L[2] / TMZ;
     ta.tc = tmarch_chunk(g);
-    dim3 grid(dslash_nblocks<C2>(g, nrhs), nrhs), blk(TMS * g.Ls);
+    dim3 grid(dslash_nblocks<C2>(g, nrhs, keep_order), nrhs), blk(TMS * g.Ls);
 #define MG_TM(DAG, MODE) \
   hipLaunchKernelGGL((k_dslash_tm<C2, DAG, MODE>), grid, blk, 0, st, in, out, b, gauge, ta, partial)
     if (!dagger && mode == 0) MG_TM(false, 0);
@@ -2569,7 +2616,7 @@ void dslash_ex(const C2* in, C2* out, const C2* b, const C2* gauge, const Geomet
     MG_LAUNCH_CHECK();
     return;
   }
-  dim3 grid(dslash_nblocks<C2>(g, nrhs), nrhs), blk(256);
+  dim3 grid(dslash_nblocks<C2>(g, nrhs, keep_order), nrhs), blk(256);
 #define MG_DS(DAG, MODE) \
   hipLaunchKernelGGL((k_dslash<C2, false, DAG, MODE>), grid, blk, 0, st, in, out, b, gauge, a, partial)
   if (!dagger && mode == 0) MG_DS(false, 0);
@@ -2592,7 +2639,7 @@ void dslash_canonical(const double2* in, double2* out, const C2* gauge, const Ge
       return;
     }
   }
-  const dim3 grid(ceil_div(g.V5, 64), nrhs), blk(256);
+  const dim3 grid(4 * ceil_div(g.V5, 256), nrhs), blk(256);
   if (dagger)
     hipLaunchKernelGGL((k_dslash<C2, true, true, 0>), grid, blk, 0, st, in, out, nullptr, gauge, a, nullptr);
   else
@@ -2607,7 +2654,7 @@ template void dslash_canonical<float2>(const double2*, double2*, const float2*, 
 template <class C2>
 void dslash(const C2* in, C2* out, const C2* b, const C2* gauge, const Geometry& g, double M5,
             double mf, bool dagger, int mode, int nrhs, hipStream_t st) {
-  dslash_ex<C2>(in, out, b, gauge, g, M5, mf, dagger, mode, nrhs, nullptr, st);
+  dslash_ex<C2>(in, out, b, gauge, g, M5, mf, dagger, mode, nrhs, nullptr, false, st);
 }
 
 void dslash_split(const double2* in, double2* out9, const double2* gauge, const Geometry& g, const int block[4],
@@ -2627,8 +2674,8 @@ template void dslash<double2>(const double2*, double2*, const double2*, const do
 template void dslash<float2>(const float2*, float2*, const float2*, const float2*, const Geometry&,
                              double, double, bool, int, int, hipStream_t);
 template void dslash_ex<double2>(const double2*, double2*, const double2*, const double2*,
-                                 const Geometry&, double, double, bool, int, int, double*, hipStream_t);
+                                 const Geometry&, double, double, bool, int, int, double*, bool, hipStream_t);
 template void dslash_ex<float2>(const float2*, float2*, const float2*, const float2*, const Geometry&,
-                                double, double, bool, int, int, double*, hipStream_t);
+                                double, double, bool, int, int, double*, bool, hipStream_t);
 
 }  // namespace mgdwf

@@ -224,8 +224,8 @@ void low_modes(mgdwf_ctx* c, const double2* v0, int nev, int m, double tol, doub
     const double yn = std::sqrt(norm2(c, y));
     scale(c, y, y, 1.0 / yn);
     if (resid) {  // |N y - lambda y| / lambda
-      dslash_ex<double2>(y, t, nullptr, c->U64.as<double2>(), c->g, c->M5, c->mf, false, 0, 1, nullptr, c->st);
-      dslash_ex<double2>(t, q, nullptr, c->U64.as<double2>(), c->g, c->M5, c->mf, true, 0, 1, nullptr, c->st);
+      dslash_ex<double2>(y, t, nullptr, c->U64.as<double2>(), c->g, c->M5, c->mf, false, 0, 1, nullptr, false, c->st);
+      dslash_ex<double2>(t, q, nullptr, c->U64.as<double2>(), c->g, c->M5, c->mf, true, 0, 1, nullptr, false, c->st);
       hipLaunchKernelGGL(k_axpby, dim3(vec_blocks(nf)), dim3(256), 0, c->st, t, q, y, 1.0, -lam, nf);
       MG_LAUNCH_CHECK();
       resid[i] = std::sqrt(norm2(c, t)) / lam;

@@ -50,6 +50,7 @@ struct CoarseGeometry {
   int Nv;        // columns per chirality
   int n2;        // 2 * Nv
   int bvol;      // 4D sites per block
+  bool planar = false;  // a 2D handle's: offsets along z and t have zero blocks
 };
 
 // Error carrying a status code through the C++ layers; converted to an

@@ -79,7 +79,9 @@ void fine_op(mgdwf_ctx* c, const F2* in, F2* out, const F2* b, bool dag, int mod
   const int nb = fine_nblocks<F2>(c, nrhs);
   if (dst >= 0) partial = c->buf<double>("dpart", (size_t)nb * nrhs);
   fine_dslash<F2>(c, in, out, b, dag, mode, nrhs, partial, c->st);
-  if (dst >= 0) finalize_rhs(partial, nb, 1, c->buf<double>("slots", (size_t)nrhs * NSLOT), dst, nrhs, c->st);
+  if (dst >= 0)
+    finalize_rhs(partial, nb, 1, c->buf<double>("slots", (size_t)nrhs * NSLOT), dst, nrhs, c->st,
+                 fine_group<F2>(c, nrhs));
   c->fine_applies += 1;
 }
 
@@ -382,14 +384,12 @@ inline void sq_op(mgdwf_ctx* c, const float2* x, float2* y, int nrhs) {
   c->coarse_applies += 1;
 }
 
-inline void l2_op(mgdwf_ctx* c, const double2* x, double2* y, int nrhs) {
-  sq_apply64(c->Acc64.as<double2>(), x, y, c->cg2, nrhs, c->st);
-  c->coarse_applies += 1;
-}
-inline void l2_op(mgdwf_ctx* c, const float2* x, float2* y, int nrhs) {
-  sq_apply32(c->Acc32.as<float2>(), x, y, c->cg2, nrhs, c->st);
-  c->coarse_applies += 1;
-}
+template <class F2> const F2* sq_matrix(mgdwf_ctx* c);  // A_c and A_cc
+template <> const double2* sq_matrix<double2>(mgdwf_ctx* c) { return c->Asq.m64.as<double2>(); }
+template <> const float2* sq_matrix<float2>(mgdwf_ctx* c) { return c->Asq.m32.as<float2>(); }
+template <class F2> const F2* l2_matrix(mgdwf_ctx* c);
+template <> const double2* l2_matrix<double2>(mgdwf_ctx* c) { return c->Acc64.as<double2>(); }
+template <> const float2* l2_matrix<float2>(mgdwf_ctx* c) { return c->Acc32.as<float2>(); }
 template <class F2> const F2* l2_basis(mgdwf_ctx* c);
 template <> const double2* l2_basis<double2>(mgdwf_ctx* c) { return c->W2_64.as<double2>(); }
 template <> const float2* l2_basis<float2>(mgdwf_ctx* c) { return c->W2_32.as<float2>(); }
@@ -401,7 +401,7 @@ struct TwoLevelSq {
   mgdwf_mg_params p;
   long long nf, nc;
   F2 *g, *ra, *rb, *t, *q, *r1, *r3;
-  F2 *cb, *cx, *cr, *cp, *cq;
+  F2 *cb, *cx, *cr, *cp, *cp2, *cq;
   double* sl;
   double* vpart;
 
@@ -420,6 +420,7 @@ struct TwoLevelSq {
     cx = c->buf<F2>("sq_cx" + tg, nc * nrhs);
     cr = c->buf<F2>("sq_cr" + tg, nc * nrhs);
     cp = c->buf<F2>("sq_cp" + tg, nc * nrhs);
+    cp2 = c->buf<F2>("sq_cp2" + tg, nc * nrhs);
     cq = c->buf<F2>("sq_cq" + tg, nc * nrhs);
     sl = c->buf<double>("slots", (size_t)nrhs * NSLOT);
     vpart = c->buf<double>("vpart", (size_t)VEC_BLOCKS * nrhs * (2 * 16 + 3));
@@ -441,39 +442,60 @@ struct TwoLevelSq {
     }
   }
 
-  // CG from x = 0 on the Hermitian operator op (vectors of n per RHS), to
-  // |r| <= tol |b| tested every 8 iterations, or maxiter; r, p, q: workspaces
-  template <class Op>
-  void cg(Op op, const F2* b, F2* x, long long n, F2* r, F2* pv, F2* qv, double tol, int maxiter) {
-    copy(c, b, r, n * nrhs);
-    copy(c, b, pv, n * nrhs);
-    norm_into<F2>(c, r, nullptr, n, nrhs, S_CRR0);
-    norm_into<F2>(c, r, nullptr, n, nrhs, S_CRR_A);
+  // CG from x = 0 on the Hermitian 33-offset operator A on lattice g, to
+  // |r| <= tol |b| tested every 8 iterations, or maxiter; r, p, p2, q: workspaces
+  void cg(const F2* A, const CoarseGeometry& g, const F2* b, F2* x, F2* r, F2* p, F2* p2, F2* q, double tol,
+          int maxiter) {
+    const long long n = (long long)g.Vc * g.n2;
+    const bool fused = !c->keep_order && sq_cg_fused(g);
+    char* work = fused ? c->buf<char>("sq_cgw", sq_cg_bytes(g, nrhs)) : nullptr;
     int cur = S_CRR_A, nxt = S_CRR_B;
+    if (fused) {
+      sq_cg_start<F2>(b, r, work, g, nrhs, c->st);
+    } else {
+      copy(c, b, r, n * nrhs);
+      copy(c, b, p, n * nrhs);
+      norm_into<F2>(c, r, nullptr, n, nrhs, S_CRR0);
+      norm_into<F2>(c, r, nullptr, n, nrhs, S_CRR_A);
+    }
     const double tol2 = tol * tol;
-    double* part = c->buf<double>("vpart", (size_t)VEC_BLOCKS * nrhs * (2 * 16 + 3));
     for (int it = 0; it < maxiter;) {
-      op(pv, qv);                                                           // q = A p
-      norm_into<F2>(c, pv, qv, n, nrhs, S_CPQ);                             // <p, q> at S_CPQ + 1
-      mr_update<F2>(x, r, pv, qv, n, nrhs, sl, cur, S_CPQ + 1, it == 0, part, c->st);  // x += a p, r -= a q
-      finalize_rhs(part, vec_blocks(n), 1, sl, nxt, nrhs, c->st);           // |r|^2
-      cg_dir<F2>(pv, r, n, nrhs, sl, nxt, cur, nullptr, c->st);             // p = r + beta p
+      if (fused) {
+        sq_cg_product<F2>(A, r, p, p2, q, work, sl, cur, nxt, S_CRR0, it == 0, g, nrhs, c->st);
+        sq_cg_update<F2>(x, r, p2, q, work, sl, nxt, it == 0, g, nrhs, c->st);
+        std::swap(p, p2);
+      } else {
+        sq_any(A, g, p, q);                                                  // q = A p
+        norm_into<F2>(c, p, q, n, nrhs, S_CPQ);                               // <p, q> at S_CPQ + 1
+        mr_update<F2>(x, r, p, q, n, nrhs, sl, cur, S_CPQ + 1, it == 0, vpart, c->st);  // x += a p, r -= a q
+        finalize_rhs(vpart, vec_blocks(n), 1, sl, nxt, nrhs, c->st);          // |r|^2
+        cg_dir<F2>(p, r, n, nrhs, sl, nxt, cur, nullptr, c->st);             // p = r + beta p
+      }
+      c->coarse_applies += 1;
       std::swap(cur, nxt);
       ++it;
       if (it % 8 == 0 && it < maxiter) {
+        const int rr = fused ? S_CPQ : cur;
+        if (fused) sq_cg_residual(work, sl, rr, g, nrhs, c->st);
         std::vector<double> h = read_slots(c, nrhs);
         bool done = true;
-        for (int rr = 0; rr < nrhs; ++rr)
-          if (!(h[rr * NSLOT + cur] <= tol2 * h[rr * NSLOT + S_CRR0])) done = false;
+        for (int k = 0; k < nrhs; ++k)
+          if (!(h[k * NSLOT + rr] <= tol2 * h[k * NSLOT + S_CRR0])) done = false;
         if (done) break;
       }
     }
+  }
+  void sq_any(const double2* A, const CoarseGeometry& g, const double2* x, double2* y) {
+    sq_apply64(A, x, y, g, nrhs, c->st, c->keep_order);
+  }
+  void sq_any(const float2* A, const CoarseGeometry& g, const float2* x, float2* y) {
+    sq_apply32(A, x, y, g, nrhs, c->st, c->keep_order);
   }
 
   // ---- third level (a level-2 basis is installed and gamma > 0): the coarse
   // solve is gamma sweeps of e <- e + K2(b - A_c e), K2 the level-2 cycle
   F2 *e2 = nullptr, *f2 = nullptr, *s2a = nullptr, *s2b = nullptr, *s2r = nullptr, *s2q = nullptr;
-  F2 *c3b = nullptr, *c3x = nullptr, *c3r = nullptr, *c3p = nullptr, *c3q = nullptr;
+  F2 *c3b = nullptr, *c3x = nullptr, *c3r = nullptr, *c3p = nullptr, *c3p2 = nullptr, *c3q = nullptr;
   long long n3 = 0;
 
   void l2_buffers() {
@@ -490,6 +512,7 @@ struct TwoLevelSq {
     c3x = c->buf<F2>("l3_x" + tg, n3 * nrhs);
     c3r = c->buf<F2>("l3_r" + tg, n3 * nrhs);
     c3p = c->buf<F2>("l3_p" + tg, n3 * nrhs);
+    c3p2 = c->buf<F2>("l3_p2" + tg, n3 * nrhs);
     c3q = c->buf<F2>("l3_q" + tg, n3 * nrhs);
   }
 
@@ -518,8 +541,7 @@ struct TwoLevelSq {
       zero<F2>(e, nc * nrhs, c->st);
     }
     restrict2<F2>(W, r1, c3b, c->cg, c->cg2, nrhs, c->st);
-    cg([&](const F2* a, F2* b) { l2_op(c, a, b, nrhs); }, c3b, c3x, n3, c3r, c3p, c3q, q.coarse_tol,
-       q.coarse_maxiter);
+    cg(l2_matrix<F2>(c), c->cg2, c3b, c3x, c3r, c3p, c3p2, c3q, q.coarse_tol, q.coarse_maxiter);
     prolong2<F2>(W, c3x, e, true, c->cg, c->cg2, nrhs, c->st);
     if (q.nu > 0) {
       sq_op(c, e, s2q, nrhs);
@@ -549,28 +571,7 @@ struct TwoLevelSq {
       coarse_solve3(b, x);
       return;
     }
-    copy(c, b, cr, nc * nrhs);
-    copy(c, b, cp, nc * nrhs);
-    norm_into<F2>(c, cr, nullptr, nc, nrhs, S_CRR0);
-    norm_into<F2>(c, cr, nullptr, nc, nrhs, S_CRR_A);
-    int cur = S_CRR_A, nxt = S_CRR_B;
-    const double tol2 = p.coarse_tol * p.coarse_tol;
-    for (int it = 0; it < p.coarse_maxiter;) {
-      sq_op(c, cp, cq, nrhs);                                               // q = A_c p
-      norm_into<F2>(c, cp, cq, nc, nrhs, S_CPQ);                            // <p, q> at S_CPQ + 1
-      mr_update<F2>(x, cr, cp, cq, nc, nrhs, sl, cur, S_CPQ + 1, it == 0, vpart, c->st);  // x += a p, r -= a q
-      finalize_rhs(vpart, vec_blocks(nc), 1, sl, nxt, nrhs, c->st);          // |r|^2
-      cg_dir<F2>(cp, cr, nc, nrhs, sl, nxt, cur, nullptr, c->st);           // p = r + beta p
-      std::swap(cur, nxt);
-      ++it;
-      if (it % 8 == 0 && it < p.coarse_maxiter) {
-        std::vector<double> h = read_slots(c, nrhs);
-        bool done = true;
-        for (int r = 0; r < nrhs; ++r)
-          if (!(h[r * NSLOT + cur] <= tol2 * h[r * NSLOT + S_CRR0])) done = false;
-        if (done) break;
-      }
-    }
+    cg(sq_matrix<F2>(c), c->cg, b, x, cr, cp, cp2, cq, p.coarse_tol, p.coarse_maxiter);
   }
 
   void apply(const F2* b, F2* z) {
@@ -818,6 +819,7 @@ void mg_solve(mgdwf_ctx* c, double2* b64, double2* x64, int nrhs, const mgdwf_so
     else solve_impl<double2, TwoLevel<double2>>(c, b64, x64, nrhs, sp, rep);
   } else if (c->mp.fine_prec == MGDWF_F32) {
     if (c->mp.coarse_prec == MGDWF_F64) fail(MGDWF_ERR_INVALID_ARG, "an FP32 fine level takes an F32/F16/BF16 coarse level");
+    const KeepOrder keep(c, c->mp.squared != 0);
     if (c->mp.squared) solve_impl<float2, TwoLevelSq<float2>>(c, b64, x64, nrhs, sp, rep);
     else solve_impl<float2, TwoLevel<float2>>(c, b64, x64, nrhs, sp, rep);
   } else {
@@ -895,6 +897,7 @@ void build_coarse_squared(mgdwf_ctx* c);                         // capi.cpp
 // operator, nh = nvec (the basis is the vectors themselves).
 void mg_setup(mgdwf_ctx* c, const mgdwf_mg_params& p, double2* W, mgdwf_setup_report* rep) {
   const int nh = p.squared ? p.nvec : p.nvec / 2;
+  const KeepOrder keep(c, p.squared != 0);
   const long long nf = c->fine_len();
   auto t0 = std::chrono::steady_clock::now();
   int nsw = 0;
@@ -995,6 +998,7 @@ void setup_level2(mgdwf_ctx* c, const mgdwf_level2_params& p, const double2* W0,
        "the third level needs the squared coarse operator (a squared setup or mgdwf_build_coarse_squared)");
   const CoarseGeometry& cg = c->cg;
   CoarseGeometry c2{};
+  c2.planar = cg.planar;
   c2.bvol = 1;
   c2.Vc = 1;
   for (int m = 0; m < 4; ++m) {

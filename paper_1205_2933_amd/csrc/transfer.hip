@@ -36,11 +36,11 @@ struct BlockArgs {
 // half the CUs idle.
 int restrict_splits(const CoarseGeometry& cg) { return std::max(4, std::min(16, 2048 / std::max(1, cg.Vc))); }
 
-BlockArgs make_args(const Geometry& g, const CoarseGeometry& cg) {
+BlockArgs make_args(const Geometry& g, const CoarseGeometry& cg, bool keep_order = false) {
   BlockArgs a;
   for (int m = 0; m < 4; ++m) { a.L[m] = g.L[m]; a.b[m] = cg.block[m]; a.Lc[m] = cg.Lc[m]; }
   a.Ls = g.Ls; a.V4 = g.V4; a.V5 = g.V5; a.Vc = cg.Vc; a.bvol = cg.bvol; a.Nv = cg.Nv;
-  a.nsplit = restrict_splits(cg);
+  a.nsplit = keep_order ? 4 : restrict_splits(cg);
   return a;
 }
 
@@ -280,6 +280,231 @@ __global__ __launch_bounds__(256) void k_restrict_mfma(const C2* __restrict__ V,
       }
 }
 
+// ---- restriction and Gram sums in one fixed order (keep_order in ctx.h)
+//
+// Multi-RHS restriction: as k_restrict, for RG right-hand sides per workgroup
+// (blockIdx.y picks the group).  A thread keeps the rows of its RG right-hand
+// sides in registers while it sweeps KR basis columns, so the basis is read
+// once per group of right-hand sides and x once per KR columns.  FP32 fields
+// are read two s-values per 16-byte load.  Partial sums in the field's
+// precision per thread (a handful of rows), FP64 across threads; same partial
+// layout as k_restrict.  k_restrict_mfma is two to three times as fast (its figures
+// are there) and adds in another order.
+template <class C2, int RG, int KR>
+__global__ __launch_bounds__(256) void k_restrict_mr(const C2* __restrict__ V, const C2* __restrict__ x,
+                                                     double* __restrict__ partial, BlockArgs a, int nrhs) {
+  using T = typename real_of<C2>::type;
+  constexpr int W = sizeof(T) == 4 ? 2 : 1;  // consecutive s per load
+  const int B = blockIdx.x / a.nsplit, split = blockIdx.x % a.nsplit;
+  const int r0 = blockIdx.y * RG;
+  const int nr = min(RG, nrhs - r0);
+  const long long V5 = a.V5;
+  const long long field = 12 * V5;
+  const int n5 = a.bvol * a.Ls;
+  const int n2 = 2 * a.Nv;
+  __shared__ double red[4][RG * 2 * KR * 2];
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  auto load = [&](const C2* f, long long off, C2 out[W]) {
+    if constexpr (W == 2) {
+      const float4 q = *reinterpret_cast<const float4*>(f + off);
+      out[0] = cmk<C2>(q.x, q.y);
+      out[1] = cmk<C2>(q.z, q.w);
+    } else {
+      out[0] = f[off];
+    }
+  };
+  for (int k0 = 0; k0 < a.Nv; k0 += KR) {
+    T acc[RG][2][KR][2];
+#pragma unroll
+    for (int r = 0; r < RG; ++r)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int kk = 0; kk < KR; ++kk) { acc[r][h][kk][0] = 0; acc[r][h][kk][1] = 0; }
+    for (int j = split * 256 + threadIdx.x; j * W < n5; j += 256 * a.nsplit) {
+      const int jj = j * W;
+      const int jl = jj / a.Ls, s = jj - jl * a.Ls;
+      const long long i5 = (long long)block_site(a, B, jl) * a.Ls + s;
+      C2 xv[RG][12][W];
+#pragma unroll
+      for (int r = 0; r < RG; ++r)
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+          if (r < nr) load(x + (long long)(r0 + r) * field, c * V5 + i5, xv[r][c]);
+          else for (int q = 0; q < W; ++q) xv[r][c][q] = cmk<C2>(0, 0);
+        }
+#pragma unroll
+      for (int kk = 0; kk < KR; ++kk) {
+        const int k = k0 + kk;
+        if (k < a.Nv) {
+#pragma unroll
+          for (int c = 0; c < 12; ++c) {
+            C2 v[W];
+            load(V + (long long)k * field, c * V5 + i5, v);
+            const int h = c / 6;
+#pragma unroll
+            for (int r = 0; r < RG; ++r)
+#pragma unroll
+              for (int q = 0; q < W; ++q) {
+                acc[r][h][kk][0] += v[q].x * xv[r][c][q].x + v[q].y * xv[r][c][q].y;
+                acc[r][h][kk][1] += v[q].x * xv[r][c][q].y - v[q].y * xv[r][c][q].x;
+              }
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < RG; ++r)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int kk = 0; kk < KR; ++kk)
+#pragma unroll
+          for (int ri = 0; ri < 2; ++ri) {
+            const double v = wave_sum((double)acc[r][h][kk][ri]);
+            if (l == 0) red[w][((r * 2 + h) * KR + kk) * 2 + ri] = v;
+          }
+    __syncthreads();
+    for (int q = threadIdx.x; q < RG * 2 * KR * 2; q += 256) {
+      const int r = q / (2 * KR * 2), h = (q / (KR * 2)) % 2, kk = (q / 2) % KR, ri = q & 1;
+      const int k = k0 + kk;
+      const double sum = red[0][q] + red[1][q] + red[2][q] + red[3][q];
+      if (k < a.Nv && r < nr)
+        partial[(((long long)(r0 + r) * a.Vc + B) * a.nsplit + split) * 2 * n2 + (h * a.Nv + k) * 2 + ri] = sum;
+    }
+    __syncthreads();
+  }
+}
+
+// Multi-RHS restriction, FP32, basis and fields each read once: a 768-thread
+// workgroup owns a quarter of block B's rows.  Per chunk of 64 rows the
+// workgroup stages the rows of up to RX right-hand sides in LDS (layout
+// [rhs][component][row], so a wavefront reads 64 consecutive rows); wave w
+// then accumulates basis columns w and w + 12 against every staged
+// right-hand side, lane = row.  Sums in FP32 within the workgroup (16 chunks
+// x 6 components per lane, then 64 lanes), FP64 across workgroups; same
+// partial layout as k_restrict.
+constexpr int RX = 12, RW = 12, RT = 64 * RW;
+__global__ __launch_bounds__(RT) void k_restrict_lds(const float2* __restrict__ V, const float2* __restrict__ x,
+                                                     double* __restrict__ partial, BlockArgs a, int nrhs) {
+  constexpr int KW = 2;  // columns per wave: 12 waves x 2 = 24 >= Nv
+  __shared__ float2 xs[RX * 12 * 64];
+  const int B = blockIdx.x / a.nsplit, split = blockIdx.x % a.nsplit;
+  const int r0 = blockIdx.y * RX;
+  const int nr = min(RX, nrhs - r0);
+  const long long V5 = a.V5;
+  const long long field = 12 * V5;
+  const int n5 = a.bvol * a.Ls;
+  const int n2 = 2 * a.Nv;
+  const int per = n5 / a.nsplit;  // rows of this workgroup (n5 divides by 256)
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  float acc[KW][RX][2][2];
+#pragma unroll
+  for (int j = 0; j < KW; ++j)
+#pragma unroll
+    for (int r = 0; r < RX; ++r)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) { acc[j][r][h][0] = 0.f; acc[j][r][h][1] = 0.f; }
+  for (int c0 = 0; c0 < per; c0 += 64) {
+    __syncthreads();  // the previous chunk's rows are consumed
+    for (int q = threadIdx.x; q < nr * 12 * 64; q += RT) {
+      const int row = q & 63, rc = q >> 6;  // rc = r * 12 + component
+      const int jj = split * per + c0 + row;
+      const int jl = jj / a.Ls, s = jj - jl * a.Ls;
+      const long long i5 = (long long)block_site(a, B, jl) * a.Ls + s;
+      const int r = rc / 12, c = rc - r * 12;
+      xs[q] = x[(long long)(r0 + r) * field + c * V5 + i5];
+    }
+    __syncthreads();
+    const int jj = split * per + c0 + l;
+    const int jl = jj / a.Ls, s = jj - jl * a.Ls;
+    const long long i5 = (long long)block_site(a, B, jl) * a.Ls + s;
+#pragma unroll
+    for (int c = 0; c < 12; ++c) {
+      const int h = c / 6;
+      float2 v[KW];
+#pragma unroll
+      for (int j = 0; j < KW; ++j) {
+        const int k = w + RW * j;
+        v[j] = k < a.Nv ? V[(long long)k * field + c * V5 + i5] : make_float2(0.f, 0.f);
+      }
+#pragma unroll
+      for (int r = 0; r < RX; ++r) {
+        if (r < nr) {
+          const float2 xv = xs[(r * 12 + c) * 64 + l];
+#pragma unroll
+          for (int j = 0; j < KW; ++j) {
+            acc[j][r][h][0] += v[j].x * xv.x + v[j].y * xv.y;
+            acc[j][r][h][1] += v[j].x * xv.y - v[j].y * xv.x;
+          }
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < KW; ++j) {
+    const int k = w + RW * j;
+#pragma unroll
+    for (int r = 0; r < RX; ++r)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int ri = 0; ri < 2; ++ri) {
+          const float sum = wave_sum(acc[j][r][h][ri]);
+          if (l == 0 && k < a.Nv && r < nr)
+            partial[(((long long)(r0 + r) * a.Vc + B) * a.nsplit + split) * 2 * n2 + (h * a.Nv + k) * 2 + ri] = sum;
+        }
+  }
+}
+
+// Gram matrix of every (block, chirality) panel, in k_chol_inv's layout: <v_i, v_j>
+// over the block's sites, all s, the six spin-colour components of chi.
+constexpr int GRAM_ROWS = 16;  // fine rows staged per LDS chunk (one row = one 5D site, 6 comps)
+
+__global__ __launch_bounds__(256) void k_gram(const double2* __restrict__ V, double2* __restrict__ G,
+                                              BlockArgs a) {
+  extern __shared__ double2 lds[];  // [GRAM_ROWS * 6][Nv]
+  const int B = blockIdx.x >> 1, chi = blockIdx.x & 1;
+  const int Nv = a.Nv;
+  const long long V5 = a.V5, field = 12 * V5;
+  const int n5 = a.bvol * a.Ls;
+  const int npair = Nv * Nv;
+  double2 acc[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) acc[q] = make_double2(0.0, 0.0);
+  for (int j0 = 0; j0 < n5; j0 += GRAM_ROWS) {
+    // stage GRAM_ROWS sites x 6 comps x Nv vectors
+    for (int e = threadIdx.x; e < GRAM_ROWS * 6 * Nv; e += 256) {
+      const int k = e % Nv, rc = e / Nv, c6 = rc % 6, jj = rc / 6;
+      const int j = j0 + jj;
+      double2 v = make_double2(0.0, 0.0);
+      if (j < n5) {
+        const int jl = j / a.Ls, s = j - jl * a.Ls;
+        const long long i5 = (long long)block_site(a, B, jl) * a.Ls + s;
+        v = V[k * field + (long long)(chi * 6 + c6) * V5 + i5];
+      }
+      lds[rc * Nv + k] = v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int p = threadIdx.x + q * 256;
+      if (p < npair) {
+        const int i = p / Nv, jc = p % Nv;
+        double2 s = acc[q];
+        for (int r = 0; r < GRAM_ROWS * 6; ++r) cfmac(s, lds[r * Nv + i], lds[r * Nv + jc]);
+        acc[q] = s;
+      }
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int p = threadIdx.x + q * 256;
+    if (p < npair) G[((long long)(p % Nv) * a.Vc + B) * 2 * Nv + chi * Nv + p / Nv] = acc[q];
+  }
+}
+
 // coarse[(rhs * Vc + B) * n2 + row] = sum over splits, in fixed order.
 template <class C2>
 __global__ void k_restrict_finalize(const double* __restrict__ partial, C2* __restrict__ coarse,
@@ -500,8 +725,8 @@ __global__ __launch_bounds__(64) void k_chol_inv(const double2* __restrict__ G, 
         for (int k = i + 1; k < 32; ++k)
           if (k <= j && k < Nv) {
             const double2 rik = w[i][k];
-            s.x += rik.x * xc[k].x - rik.y * xc[k].y;
-            s.y += rik.x * xc[k].y + rik.y * xc[k].x;
+            s.x += fma(rik.x, xc[k].x, -(rik.y * xc[k].y));  // contracted as written: keep_order
+            s.y += fma(rik.x, xc[k].y, rik.y * xc[k].x);
           }
         s = make_double2(-s.x / rii, -s.y / rii);
       }
@@ -558,11 +783,24 @@ size_t restrict_partial_doubles(const CoarseGeometry& cg, int nrhs) {
 
 template <class C2, class CC2>
 void restrict_op(const C2* V, const C2* x, CC2* coarse, double* partial, const Geometry& g,
-                 const CoarseGeometry& cg, int nrhs, hipStream_t st) {
-  BlockArgs a = make_args(g, cg);
+                 const CoarseGeometry& cg, int nrhs, hipStream_t st, bool keep_order) {
+  BlockArgs a = make_args(g, cg, keep_order);
   constexpr bool f64 = sizeof(typename real_of<C2>::type) == 8;
-  // the FP32 kernel reads s-pairs: Ls even keeps every pair inside one site
-  if (nrhs >= 2 && cg.Nv <= 32 && (f64 || g.Ls % 2 == 0)) {
+  // the FP32 multi-RHS kernels read s-pairs: Ls even keeps every pair inside one site
+  if (keep_order && nrhs >= 2 && (f64 || g.Ls % 2 == 0)) {
+    constexpr int RG = 2, KR = f64 ? 4 : 6;
+    bool done = false;
+    if constexpr (!f64) {
+      // basis and fields read once; rows per workgroup a multiple of 64
+      done = cg.Nv <= 24 && (cg.bvol * g.Ls) % (64 * a.nsplit) == 0;
+      if (done)
+        hipLaunchKernelGGL(k_restrict_lds, dim3(cg.Vc * a.nsplit, ceil_div(nrhs, RX)), dim3(RT), 0, st, V, x, partial, a,
+                           nrhs);
+    }
+    if (!done)
+      hipLaunchKernelGGL((k_restrict_mr<C2, RG, KR>), dim3(cg.Vc * a.nsplit, ceil_div(nrhs, RG)), dim3(256), 0, st, V, x,
+                         partial, a, nrhs);
+  } else if (nrhs >= 2 && cg.Nv <= 32 && (f64 || g.Ls % 2 == 0)) {
     const int nt = std::min(4, ceil_div(nrhs, 8));
     const dim3 grid(cg.Vc * a.nsplit, ceil_div(nrhs, 8 * nt));
     const bool wide = g.Ls % (f64 ? 2 : 4) == 0;  // 32 bytes per lane: a group of four lanes reads whole 128-byte lines
@@ -618,9 +856,9 @@ void prolong_op(const C2* V, const CC2* coarse, C2* fine, bool accumulate, const
 }
 
 template void restrict_op<double2, double2>(const double2*, const double2*, double2*, double*,
-                                            const Geometry&, const CoarseGeometry&, int, hipStream_t);
+                                            const Geometry&, const CoarseGeometry&, int, hipStream_t, bool);
 template void restrict_op<float2, float2>(const float2*, const float2*, float2*, double*, const Geometry&,
-                                          const CoarseGeometry&, int, hipStream_t);
+                                          const CoarseGeometry&, int, hipStream_t, bool);
 template void prolong_op<double2, double2>(const double2*, const double2*, double2*, bool, const Geometry&,
                                            const CoarseGeometry&, int, hipStream_t);
 template void prolong_op<float2, float2>(const float2*, const float2*, float2*, bool, const Geometry&,
@@ -628,7 +866,7 @@ template void prolong_op<float2, float2>(const float2*, const float2*, float2*, 
 
 // Two passes of Cholesky QR on every (block, chirality) panel of the FP64 basis.
 // Returns false if any panel is numerically rank deficient.
-bool orthonormalise_basis(double2* V, const Geometry& g, const CoarseGeometry& cg, hipStream_t st) {
+bool orthonormalise_basis(double2* V, const Geometry& g, const CoarseGeometry& cg, bool keep_order, hipStream_t st) {
   if (cg.Nv > 32) fail(MGDWF_ERR_INVALID_ARG, "nvec above 32 is not supported");
   BlockArgs a = make_args(g, cg);
   const int npanel = 2 * cg.Vc;
@@ -638,7 +876,13 @@ bool orthonormalise_basis(double2* V, const Geometry& g, const CoarseGeometry& c
   std::vector<int> hs(npanel);
   bool ok = true;
   for (int pass = 0; pass < 2; ++pass) {
-    restrict_op<double2, double2>(V, V, G.as<double2>(), part.as<double>(), g, cg, cg.Nv, st);  // Gram matrices
+    if (keep_order) {
+      hipLaunchKernelGGL(k_gram, dim3(npanel), dim3(256), (size_t)GRAM_ROWS * 6 * cg.Nv * sizeof(double2), st, V,
+                         G.as<double2>(), a);
+      MG_LAUNCH_CHECK();
+    } else {
+      restrict_op<double2, double2>(V, V, G.as<double2>(), part.as<double>(), g, cg, cg.Nv, st, false);  // Gram matrices
+    }
     hipLaunchKernelGGL(k_chol_inv, dim3(npanel), dim3(64), 0, st, G.as<double2>(), W.as<double2>(), stat.as<int>(),
                        cg.Vc, cg.Nv);
     MG_LAUNCH_CHECK();

@@ -223,14 +223,19 @@ void pack_gauge_field(mgdwf_ctx* c, const double2* canon) {
 
 template <class F2>
 int fine_nblocks(const mgdwf_ctx* c, int nrhs) {
-  return c->model == 0 ? dslash_nblocks<F2>(c->g, nrhs) : ceil_div(c->g.V5, 256);
+  return c->model == 0 ? dslash_nblocks<F2>(c->g, nrhs, c->keep_order) : ceil_div(c->g.V5, 256);
+}
+
+template <class F2>
+int fine_group(const mgdwf_ctx* c, int nrhs) {
+  return c->model == 0 ? dslash_group<F2>(c->g, nrhs, c->keep_order) : 1;
 }
 
 template <class F2>
 void fine_dslash(const mgdwf_ctx* c, const F2* in, F2* out, const F2* b, bool dag, int mode, int nrhs,
                  double* partial, hipStream_t st) {
   if (c->model == 0)
-    dslash_ex<F2>(in, out, b, gauge_for<F2>(c), c->g, c->M5, c->mf, dag, mode, nrhs, partial, st);
+    dslash_ex<F2>(in, out, b, gauge_for<F2>(c), c->g, c->M5, c->mf, dag, mode, nrhs, partial, c->keep_order, st);
   else
     dwf2d<F2>(c, in, out, b, dag, mode, nrhs, partial, st);
 }
@@ -239,7 +244,7 @@ template <class F2>
 void fine_restrict(mgdwf_ctx* c, const F2* V, const F2* in, F2* out, int nrhs) {
   if (c->model == 0)
     restrict_op<F2, F2>(V, in, out, c->buf<double>("rpart", restrict_partial_doubles(c->cg, nrhs)), c->g, c->cg,
-                        nrhs, c->st);
+                        nrhs, c->st, c->keep_order);
   else
     restrict2<F2>(V, in, out, c->fg, c->cg, nrhs, c->st);
 }
@@ -251,7 +256,7 @@ void fine_prolong(mgdwf_ctx* c, const F2* V, const F2* cc, F2* out, bool acc, in
 }
 
 bool fine_orthonormalise(mgdwf_ctx* c) {
-  if (c->model == 0) return orthonormalise_basis(c->V64.as<double2>(), c->g, c->cg, c->st);
+  if (c->model == 0) return orthonormalise_basis(c->V64.as<double2>(), c->g, c->cg, c->keep_order, c->st);
   return orthonormalise_level2(c->V64.as<double2>(), c->fg, c->cg, c->buf<int>("orth_err", 1), c->st);
 }
 
@@ -276,6 +281,8 @@ void build_sq_coarse_2d(mgdwf_ctx* c) {
 
 template int fine_nblocks<double2>(const mgdwf_ctx*, int);
 template int fine_nblocks<float2>(const mgdwf_ctx*, int);
+template int fine_group<double2>(const mgdwf_ctx*, int);
+template int fine_group<float2>(const mgdwf_ctx*, int);
 template void fine_dslash<double2>(const mgdwf_ctx*, const double2*, double2*, const double2*, bool, int, int,
                                    double*, hipStream_t);
 template void fine_dslash<float2>(const mgdwf_ctx*, const float2*, float2*, const float2*, bool, int, int, double*,

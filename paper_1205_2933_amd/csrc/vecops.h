@@ -12,7 +12,9 @@ constexpr int VEC_BLOCKS = 1024; // most workgroups of a grid-stride vector kern
 // workgroups (and partial sums per RHS) of a vector kernel over n elements
 int vec_blocks(long long n);
 
-void finalize_rhs(const double* partial, int nparts, int ncomp, double* sl, int dst, int nrhs, hipStream_t st);
+// group > 1: every `group` consecutive partials are added first
+void finalize_rhs(const double* partial, int nparts, int ncomp, double* sl, int dst, int nrhs, hipStream_t st,
+                  int group = 1);
 
 template <class C2>
 void mr_update(C2* x, C2* r, const C2* p, const C2* q, long long n, int nrhs, const double* sl, int num, int den,
@@ -57,10 +59,13 @@ void reflect5(const C2* in, C2* out, const Geometry& g, int nf, hipStream_t st);
 
 // dslash.hip
 template <class C2>
-int dslash_nblocks(const Geometry& g, int nrhs);
+int dslash_nblocks(const Geometry& g, int nrhs, bool keep_order);
+// partial sums that finalize_rhs adds first (its `group`)
+template <class C2>
+int dslash_group(const Geometry& g, int nrhs, bool keep_order);
 template <class C2>
 void dslash_ex(const C2* in, C2* out, const C2* b, const C2* gauge, const Geometry& g, double M5, double mf,
-               bool dagger, int mode, int nrhs, double* partial, hipStream_t st);
+               bool dagger, int mode, int nrhs, double* partial, bool keep_order, hipStream_t st);
 // FP32 tilings: how many, and (x, y, z tile, t-slices per workgroup at nrhs
 // right-hand sides) of entry i if it applies to g, with its MGDWF_TILE_* flags.
 int dslash_ftile_count();
@@ -70,11 +75,11 @@ bool dslash_ftile_desc(const Geometry& g, int i, int nrhs, int desc[4], int* fla
 size_t restrict_partial_doubles(const CoarseGeometry& cg, int nrhs);
 template <class C2, class CC2>
 void restrict_op(const C2* V, const C2* x, CC2* coarse, double* partial, const Geometry& g,
-                 const CoarseGeometry& cg, int nrhs, hipStream_t st);
+                 const CoarseGeometry& cg, int nrhs, hipStream_t st, bool keep_order = false);
 template <class C2, class CC2>
 void prolong_op(const C2* V, const CC2* coarse, C2* fine, bool accumulate, const Geometry& g,
                 const CoarseGeometry& cg, int nrhs, hipStream_t st);
-bool orthonormalise_basis(double2* V, const Geometry& g, const CoarseGeometry& cg, hipStream_t st);
+bool orthonormalise_basis(double2* V, const Geometry& g, const CoarseGeometry& cg, bool keep_order, hipStream_t st);
 
 // coarse.hip
 int coarse_build_columns(const Geometry& g);  // columns built together (sizes the builds' workspaces)
@@ -128,8 +133,27 @@ void build_sq_coarse_op(const double2* Vhat, const double2* gauge, double2* Ac, 
                         double mf, hipStream_t st);
 void sq_to_f32(const double2* Ac, float2* Ac32, const CoarseGeometry& cg, hipStream_t st);
 void sq_canonical(const double2* Ac, double2* out, const CoarseGeometry& cg, hipStream_t st);
-void sq_apply64(const double2* Ac, const double2* x, double2* y, const CoarseGeometry& cg, int nrhs, hipStream_t st);
-void sq_apply32(const float2* Ac32, const float2* x, float2* y, const CoarseGeometry& cg, int nrhs, hipStream_t st);
+void sq_apply64(const double2* Ac, const double2* x, double2* y, const CoarseGeometry& cg, int nrhs, hipStream_t st,
+                bool keep_order = false);
+template <class O2>  // y as FP32 or FP64 complex
+void sq_apply32(const float2* Ac32, const float2* x, O2* y, const CoarseGeometry& cg, int nrhs, hipStream_t st,
+                bool keep_order = false);
+// CG on a 33-offset operator as two launches per iteration (2 Nv a multiple of
+// 16).  work: sq_cg_bytes.  start: r = b.  product: p_new = r + beta p_old, q = A
+// p_new, with |r|^2 into slot nxt (and rr0 when first; beta = |r|^2 / slot cur, 0
+// when first).  update: x (+)= alpha p, r -= alpha q, alpha = slot rr / <p, q>.
+// residual: |r|^2 after the last update into slot dst.
+bool sq_cg_fused(const CoarseGeometry& cg);
+size_t sq_cg_bytes(const CoarseGeometry& cg, int nrhs);
+template <class F2>
+void sq_cg_start(const F2* b, F2* r, void* work, const CoarseGeometry& cg, int nrhs, hipStream_t st);
+template <class F2>
+void sq_cg_product(const F2* A, const F2* r, const F2* p_old, F2* p_new, F2* q, void* work, double* sl, int cur, int nxt,
+                   int rr0, bool first, const CoarseGeometry& cg, int nrhs, hipStream_t st);
+template <class F2>
+void sq_cg_update(F2* x, F2* r, const F2* p, const F2* q, void* work, double* sl, int rr, bool first,
+                  const CoarseGeometry& cg, int nrhs, hipStream_t st);
+void sq_cg_residual(void* work, double* sl, int dst, const CoarseGeometry& cg, int nrhs, hipStream_t st);
 
 // level2.hip: a third level under the squared method.  cg: the coarse lattice
 // (level 1), c2: the level-2 lattice (Lc = blocks, Vc = blocks, Nv = Nv2,

@@ -18,16 +18,22 @@ namespace {
 
 __device__ __forceinline__ double slot(const double* sl, int rhs, int i) { return sl[rhs * NSLOT + i]; }
 
-// out[rhs * NSLOT + dst + comp] = sum_i partial[(rhs * nparts + i) * ncomp + comp].
-// One workgroup per sum, bound by load latency: BS 1024 and eight loads in
-// flight where there are many partials (the plain Dslash leaves V5 / 64).
-template <int BS>
+// out[rhs * NSLOT + dst + comp] = sum_i partial[(rhs * nparts + i) * ncomp + comp],
+// every G consecutive i added first (the plain Dslash leaves four partials per 256
+// sites).  One workgroup per sum, bound by load latency: eight loads in flight.
+template <int BS, int G>
 __global__ __launch_bounds__(BS) void k_finalize_rhs(const double* __restrict__ partial, int nparts, int ncomp,
                                                      double* __restrict__ sl, int dst) {
   const int comp = blockIdx.x, rhs = blockIdx.y;
+  const double* p = partial + (long long)rhs * nparts * ncomp + comp;
   double acc = 0.0;
 #pragma unroll 8
-  for (int i = threadIdx.x; i < nparts; i += BS) acc += partial[((long long)rhs * nparts + i) * ncomp + comp];
+  for (int i = threadIdx.x; i < nparts / G; i += BS) {
+    double s = p[(long long)i * G * ncomp];
+#pragma unroll
+    for (int k = 1; k < G; ++k) s += p[((long long)i * G + k) * ncomp];
+    acc += s;
+  }
   acc = block_sum<BS>(acc);
   if (threadIdx.x == 0) sl[rhs * NSLOT + dst + comp] = acc;
 }
@@ -369,11 +375,12 @@ __global__ void k_reflect5(const C2* __restrict__ in, C2* __restrict__ out, long
 
 int vec_blocks(long long n) { return std::max(1, std::min(ceil_div(n, 256), VEC_BLOCKS)); }
 
-void finalize_rhs(const double* partial, int nparts, int ncomp, double* sl, int dst, int nrhs, hipStream_t st) {
-  if (nparts > 2048)
-    hipLaunchKernelGGL(k_finalize_rhs<1024>, dim3(ncomp, nrhs), dim3(1024), 0, st, partial, nparts, ncomp, sl, dst);
+void finalize_rhs(const double* partial, int nparts, int ncomp, double* sl, int dst, int nrhs, hipStream_t st,
+                  int group) {
+  if (group == 4)
+    hipLaunchKernelGGL((k_finalize_rhs<256, 4>), dim3(ncomp, nrhs), dim3(256), 0, st, partial, nparts, ncomp, sl, dst);
   else
-    hipLaunchKernelGGL(k_finalize_rhs<256>, dim3(ncomp, nrhs), dim3(256), 0, st, partial, nparts, ncomp, sl, dst);
+    hipLaunchKernelGGL((k_finalize_rhs<256, 1>), dim3(ncomp, nrhs), dim3(256), 0, st, partial, nparts, ncomp, sl, dst);
   MG_LAUNCH_CHECK();
 }
 

@@ -466,10 +466,11 @@ struct TwoLevelSq {
         std::swap(p, p2);
       } else {
         sq_any(A, g, p, q);                                                  // q = A p
-        norm_into<F2>(c, p, q, n, nrhs, S_CPQ);                               // <p, q> at S_CPQ + 1
-        mr_update<F2>(x, r, p, q, n, nrhs, sl, cur, S_CPQ + 1, it == 0, vpart, c->st);  // x += a p, r -= a q
-        finalize_rhs(vpart, vec_blocks(n), 1, sl, nxt, nrhs, c->st);          // |r|^2
-        cg_dir<F2>(p, r, n, nrhs, sl, nxt, cur, nullptr, c->st);             // p = r + beta p
+        // partials of |p|^2, <p, q>, then of |r|^2: the launch that needs a sum adds them
+        double* rpart = vpart + (size_t)nrhs * vec_blocks(n) * 3;
+        multidot_rhs<F2>(nullptr, 0, p, q, n, nrhs, vpart, sl, -1, c->st);
+        mr_update<F2>(x, r, p, q, n, nrhs, sl, cur, 0, it == 0, rpart, c->st, vpart + 1, 3);  // x += a p, r -= a q
+        cg_dir<F2>(p, r, n, nrhs, sl, nxt, cur, nullptr, c->st, rpart);                       // p = r + beta p
       }
       c->coarse_applies += 1;
       std::swap(cur, nxt);

@@ -209,6 +209,67 @@ __global__ __launch_bounds__(576) void k_sq_apply(const MC2* __restrict__ M, con
   }
 }
 
+// The same sums bit for bit (FP32, 2 Nv = N2 a multiple of 16), for keep_order:
+// as above, but blockIdx.y picks NR right-hand sides, the vector entries, the same
+// for a whole wavefront, come as scalar loads (no panel, no barrier before the final
+// sum) and KC columns are in flight ahead of those being multiplied.  Bound by load
+// latency at few sites, by the bytes of M at many.
+template <int N2, int NR>
+__global__ __launch_bounds__(576) void k_sq_ordered(const float2* __restrict__ M, const float2* __restrict__ x,
+                                                    float2* __restrict__ y, SqArgs a, int nrhs) {
+  constexpr int KC = N2 == 48 ? 12 : 8;
+  __shared__ float2 sum[9][NR][64];
+  const int X = blockIdx.x, r0 = blockIdx.y * NR;
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), l = threadIdx.x & 63;
+  const long long vs = (long long)a.Vc * N2;
+  float2 m0[KC], m1[KC];
+  const auto hold = [] { asm volatile("" ::: "memory"); };  // loads stay where they stand (registers)
+  const unsigned lane_off = (unsigned)(l < N2 ? l : N2 - 1) * sizeof(float2);
+  auto fetch = [&](float2* m, int o, int c0) {  // wave-uniform base, 32-bit lane offset
+    const char* Mo = reinterpret_cast<const char*>(M + (((long long)X * 33 + o) * N2 + c0) * N2);
+#pragma unroll
+    for (int c = 0; c < KC; ++c) m[c] = *reinterpret_cast<const float2*>(Mo + c * N2 * sizeof(float2) + lane_off);
+  };
+  float2 acc[NR];
+#pragma unroll
+  for (int j = 0; j < NR; ++j) acc[j] = make_float2(0.f, 0.f);
+  auto multiply = [&](const float2* m, const float2* xo) {
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+      const float2* xv = xo + (long long)(r0 + j < nrhs ? j : 0) * vs;
+#pragma unroll
+      for (int c = 0; c < KC; ++c) cfma(acc[j], m[c], xv[c]);
+    }
+  };
+  fetch(m0, w, 0);
+#pragma unroll 1
+  for (int o = w; o < 33; o += 9) {
+    const float2* xo = x + (long long)r0 * vs + (long long)sq_neighbour(a, X, o) * N2;
+#pragma unroll 1
+    for (int c = 0; c < N2; c += 2 * KC) {
+      fetch(m1, o, c + KC);
+      hold();
+      multiply(m0, xo + c);
+      hold();
+      if (c + 2 * KC < N2) fetch(m0, o, c + 2 * KC);
+      else if (o + 9 < 33) fetch(m0, o + 9, 0);
+      hold();
+      multiply(m1, xo + c + KC);
+      hold();
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < NR; ++j) sum[w][j][l] = acc[j];
+  __syncthreads();
+  for (int e = threadIdx.x; e < NR * 64; e += 576) {
+    const int j = e >> 6, row = e & 63;
+    float2 s = sum[0][j][row];
+#pragma unroll
+    for (int q = 1; q < 9; ++q) s = cadd(s, sum[q][j][row]);
+    if (row < N2 && r0 + j < nrhs) y[(long long)(r0 + j) * vs + (long long)X * N2 + row] = s;
+  }
+}
+
 // ---- the product on MFMA (2 Nv a multiple of 16), alone or as a CG step
 //
 // A workgroup of SQW wavefronts owns 16 RT rows of one coarse site (blockIdx.y picks
@@ -600,6 +661,24 @@ void sq_apply64(const double2* Ac, const double2* x, double2* y, const CoarseGeo
   }
 }
 
+static bool sq_ordered_launch(const float2* A, const float2* x, float2* y, const SqArgs& a, const CoarseGeometry& cg, int nrhs,
+                              hipStream_t st) {
+  const bool done = with_sq_n2(cg.n2, [&](auto N) {
+    constexpr int N2 = decltype(N)::value;
+    const dim3 blk(576);
+#define MG_SQO(NR) \
+  hipLaunchKernelGGL((k_sq_ordered<N2, NR>), dim3(cg.Vc, ceil_div(nrhs, NR)), blk, 0, st, A, x, y, a, nrhs)
+    const int nr = ceil_div(nrhs * cg.Vc, 256);  // right-hand sides a workgroup takes with one for every CU
+    if (nr <= 1) MG_SQO(1);
+    else if (nr <= 2) MG_SQO(2);
+    else if (nr <= 4) MG_SQO(4);
+    else MG_SQO(8);
+#undef MG_SQO
+  });
+  if (done) MG_LAUNCH_CHECK();
+  return done;
+}
+
 template <class O2>
 void sq_apply32(const float2* Ac32, const float2* x, O2* y, const CoarseGeometry& cg, int nrhs, hipStream_t st,
                 bool keep_order) {
@@ -608,6 +687,8 @@ void sq_apply32(const float2* Ac32, const float2* x, O2* y, const CoarseGeometry
   q.x = x;
   if (!keep_order && sq_mfma_launch<float2, O2, false>(Ac32, y, q, cg, nrhs, st)) return;
   const SqArgs a = sq_args(cg);
+  if constexpr (std::is_same<O2, float2>::value)
+    if (keep_order && sq_ordered_launch(Ac32, x, y, a, cg, nrhs, st)) return;
   for (int r0 = 0; r0 < nrhs; r0 += 16) {
     const int nr = std::min(16, nrhs - r0);
     if (nr == 1) sq_launch<float2, float2, 1>(Ac32, x, y, a, cg.Vc, nrhs, r0, st);

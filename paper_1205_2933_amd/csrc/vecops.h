@@ -16,12 +16,14 @@ int vec_blocks(long long n);
 void finalize_rhs(const double* partial, int nparts, int ncomp, double* sl, int dst, int nrhs, hipStream_t st,
                   int group = 1);
 
+// sums: <p, q> as partials (one per vec_blocks workgroup, ncomp apart) in place of slot den
 template <class C2>
 void mr_update(C2* x, C2* r, const C2* p, const C2* q, long long n, int nrhs, const double* sl, int num, int den,
-               bool first, double* partial, hipStream_t st);
+               bool first, double* partial, hipStream_t st, const double* sums = nullptr, int ncomp = 1);
+// sums: |r|^2 as partials, put into slot num by the way
 template <class C2>
-void cg_dir(C2* p, const C2* r, long long n, int nrhs, const double* sl, int num, int den, double* partial,
-            hipStream_t st);
+void cg_dir(C2* p, const C2* r, long long n, int nrhs, double* sl, int num, int den, double* partial,
+            hipStream_t st, const double* sums = nullptr);
 template <class C2>
 void res_update(C2* rout, const C2* rin, const C2* q, long long n, int nrhs, const double* sl, int num, int den,
                 hipStream_t st);

@@ -39,14 +39,28 @@ __global__ __launch_bounds__(BS) void k_finalize_rhs(const double* __restrict__ 
 }
 
 // x (+)= alpha p;  r -= alpha q;  alpha = sl[num] / sl[den] (real);  partial |r|^2.
+// Slot `s`, or with np > 0 the sum that finalize_rhs would put there (its order),
+// added from the np partials by every workgroup: one launch less where they are few.
+__device__ __forceinline__ double slot_or_sum(const double* sl, int rhs, int s, const double* part, int np, int ncomp) {
+  if (np == 0) return slot(sl, rhs, s);
+  __shared__ double tot;
+  double acc = 0.0;
+  for (int i = threadIdx.x; i < np; i += 256) acc += part[((long long)rhs * np + i) * ncomp];
+  acc = block_sum<256>(acc);
+  if (threadIdx.x == 0) tot = acc;
+  __syncthreads();
+  return tot;
+}
+
 template <class C2>
 __global__ __launch_bounds__(256) void k_mr_update(C2* __restrict__ x, C2* __restrict__ r, const C2* __restrict__ p,
                                                    const C2* __restrict__ q, long long n, const double* __restrict__ sl,
-                                                   int num, int den, int first, double* __restrict__ partial) {
+                                                   int num, int den, int first, double* __restrict__ partial,
+                                                   const double* __restrict__ sums, int np, int ncomp) {
   using T = typename real_of<C2>::type;
   const int rhs = blockIdx.y;
   const long long off = rhs * n;
-  const double dd = slot(sl, rhs, den);
+  const double dd = slot_or_sum(sl, rhs, den, sums, np, ncomp);
   const T alpha = (T)(dd > 0.0 ? slot(sl, rhs, num) / dd : 0.0);
   double nr = 0.0;
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
@@ -150,39 +164,43 @@ __global__ __launch_bounds__(256) void k_lincomb(C2* __restrict__ x, const C2* c
 // p = r + beta p, beta = sl[num] / sl[den]  (CG direction update); partial |p|^2
 template <class C2>
 __global__ __launch_bounds__(256) void k_cg_dir(C2* __restrict__ p, const C2* __restrict__ r, long long n,
-                                                const double* __restrict__ sl, int num, int den,
-                                                double* __restrict__ partial) {
+                                                double* __restrict__ sl, int num, int den,
+                                                double* __restrict__ partial, const double* __restrict__ sums,
+                                                int np) {
   using T = typename real_of<C2>::type;
   const int rhs = blockIdx.y;
   const long long off = rhs * n;
+  const double nn = slot_or_sum(sl, rhs, num, sums, np, 1);
+  if (np > 0 && blockIdx.x == 0 && threadIdx.x == 0) sl[(long long)rhs * NSLOT + num] = nn;
   const double dd = slot(sl, rhs, den);
-  const T beta = (T)(dd > 0.0 ? slot(sl, rhs, num) / dd : 0.0);
-  double np = 0.0;
+  const T beta = (T)(dd > 0.0 ? nn / dd : 0.0);
+  double pp = 0.0;
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
     C2 v = cadd(r[off + i], cscale(p[off + i], beta));
     p[off + i] = v;
-    np += (double)v.x * v.x + (double)v.y * v.y;
+    pp += (double)v.x * v.x + (double)v.y * v.y;
   }
   if (partial) {
-    double s = block_sum<256>(np);
+    double s = block_sum<256>(pp);
     if (threadIdx.x == 0) partial[(long long)rhs * gridDim.x + blockIdx.x] = s;
   }
 }
 
 // Multi-dot: partial[rhs][blk][2m..] = <a_m, b> (complex) for m < nv, then |b|^2 and
 // <b, c> (complex) when c is non-null.  Layout of the ncomp = 2 nv + 3 components:
-// [re0, im0, ..., |b|^2, re_bc, im_bc].
-template <class C2>
+// [re0, im0, ..., |b|^2, re_bc, im_bc].  DOTS false: nv is 0 (smoother and CG sums).
+template <class C2, bool DOTS>
 __global__ __launch_bounds__(256) void k_multidot(const C2* const* __restrict__ avec, int nv, const C2* __restrict__ b,
                                                   const C2* __restrict__ c, long long n,
                                                   double* __restrict__ partial) {
-  constexpr int MAXV = 16;
+  constexpr int MAXV = DOTS ? 16 : 0;
   const int rhs = blockIdx.y;
   const long long off = rhs * n;
-  double re[MAXV], im[MAXV];
+  double re[DOTS ? MAXV : 1], im[DOTS ? MAXV : 1];
 #pragma unroll
   for (int m = 0; m < MAXV; ++m) { re[m] = 0.0; im[m] = 0.0; }
   double nn = 0.0, cr = 0.0, cim = 0.0;
+#pragma unroll DOTS ? 1 : 4
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
     C2 bv = b[off + i];
     const double bx = bv.x, by = bv.y;
@@ -203,7 +221,7 @@ __global__ __launch_bounds__(256) void k_multidot(const C2* const* __restrict__ 
   }
   const int ncomp = 2 * nv + 3;
   double* out = partial + ((long long)rhs * gridDim.x + blockIdx.x) * ncomp;
-  for (int m = 0; m < nv; ++m) {
+  for (int m = 0; DOTS && m < nv; ++m) {
     double sr = block_sum<256>(re[m]);
     double si = block_sum<256>(im[m]);
     if (threadIdx.x == 0) { out[2 * m] = sr; out[2 * m + 1] = si; }
@@ -386,9 +404,9 @@ void finalize_rhs(const double* partial, int nparts, int ncomp, double* sl, int 
 
 template <class C2>
 void mr_update(C2* x, C2* r, const C2* p, const C2* q, long long n, int nrhs, const double* sl, int num, int den,
-               bool first, double* partial, hipStream_t st) {
+               bool first, double* partial, hipStream_t st, const double* sums, int ncomp) {
   hipLaunchKernelGGL(k_mr_update<C2>, dim3(vec_blocks(n), nrhs), dim3(256), 0, st, x, r, p, q, n, sl, num, den,
-                     first ? 1 : 0, partial);
+                     first ? 1 : 0, partial, sums, sums ? vec_blocks(n) : 0, ncomp);
   MG_LAUNCH_CHECK();
 }
 
@@ -427,9 +445,10 @@ void lincomb(C2* x, const C2* const* ps, int nv, long long n, int nrhs, const do
 }
 
 template <class C2>
-void cg_dir(C2* p, const C2* r, long long n, int nrhs, const double* sl, int num, int den, double* partial,
-            hipStream_t st) {
-  hipLaunchKernelGGL(k_cg_dir<C2>, dim3(vec_blocks(n), nrhs), dim3(256), 0, st, p, r, n, sl, num, den, partial);
+void cg_dir(C2* p, const C2* r, long long n, int nrhs, double* sl, int num, int den, double* partial,
+            hipStream_t st, const double* sums) {
+  hipLaunchKernelGGL(k_cg_dir<C2>, dim3(vec_blocks(n), nrhs), dim3(256), 0, st, p, r, n, sl, num, den, partial, sums,
+                     sums ? vec_blocks(n) : 0);
   MG_LAUNCH_CHECK();
 }
 
@@ -437,9 +456,12 @@ template <class C2>
 void multidot_rhs(const C2* const* avec, int nv, const C2* b, const C2* c, long long n, int nrhs, double* partial,
                   double* sl, int dst, hipStream_t st) {
   if (nv > 16) fail(MGDWF_ERR_INVALID_ARG, "at most 16 Krylov vectors per restart");
-  hipLaunchKernelGGL(k_multidot<C2>, dim3(vec_blocks(n), nrhs), dim3(256), 0, st, avec, nv, b, c, n, partial);
+  if (nv > 0)
+    hipLaunchKernelGGL((k_multidot<C2, true>), dim3(vec_blocks(n), nrhs), dim3(256), 0, st, avec, nv, b, c, n, partial);
+  else
+    hipLaunchKernelGGL((k_multidot<C2, false>), dim3(vec_blocks(n), nrhs), dim3(256), 0, st, avec, nv, b, c, n, partial);
   MG_LAUNCH_CHECK();
-  finalize_rhs(partial, vec_blocks(n), 2 * nv + 3, sl, dst, nrhs, st);
+  if (dst >= 0) finalize_rhs(partial, vec_blocks(n), 2 * nv + 3, sl, dst, nrhs, st);
 }
 
 template <class C2>
@@ -506,8 +528,8 @@ void reflect5(const C2* in, C2* out, const Geometry& g, int nf, hipStream_t st) 
 
 #define MG_INST(C2)                                                                                              \
   template void mr_update<C2>(C2*, C2*, const C2*, const C2*, long long, int, const double*, int, int, bool,    \
-                              double*, hipStream_t);                                                             \
-  template void cg_dir<C2>(C2*, const C2*, long long, int, const double*, int, int, double*, hipStream_t);      \
+                              double*, hipStream_t, const double*, int);                                                             \
+  template void cg_dir<C2>(C2*, const C2*, long long, int, double*, int, int, double*, hipStream_t, const double*);      \
   template void res_update<C2>(C2*, const C2*, const C2*, long long, int, const double*, int, int, hipStream_t); \
   template void lincomb_c<C2>(C2*, const C2* const*, int, long long, int, const double2*, hipStream_t);        \
   template void lincomb<C2>(C2*, const C2* const*, int, long long, int, const double*, int, bool, hipStream_t);        \

@@ -156,8 +156,11 @@ struct DslashArgs {
 // relies on (keep_order in ctx.h).
 // Bound by the latency of its one round of loads on small lattices (4^4x8, FP64:
 // 3.9 us, 8.8 with one thread per site and all eight hops in a row), by L2 reads
-// on large ones (16^3x32x16, FP64: 410 us per field, every neighbour and link
-// loaded by every lane; links staged once per site in LDS: 485 us).
+// on large ones (8^3x16x16, FP64, four fields: 79 us against 86; every neighbour
+// and link is loaded by every lane, and links staged once per site in LDS were
+// slower).  A sum per direction, added at the end, is 13 % faster on small odd FP32
+// lattices (9x7x5x11x5, three fields, a whole call: 22.2 against 25.3 us; 36.4 with
+// one thread per site) but adds in another order.
 // CANON: in and out are canonical FP64 fields (site major, all 12 components of
 // a site together), converted on the way, so a call on a small lattice is one
 // launch.

@@ -142,7 +142,11 @@ __global__ __launch_bounds__(256) void k_restrict(const C2* __restrict__ V, cons
 // 1.87 against 2.48 ms with FP32 tiles).  FP32 rows are widened and go through the
 // same FP64 tiles: the matrix rate is spare (FP32 tiles 1.88 ms, FP64 1.97 on that
 // case) and the sums are exact to the inputs' rounding (4.4e-8 against 64 bits,
-// 8.6e-8 to 2.0e-7 in the VALU form).  Bound by HBM at few right-hand sides, by
+// 8.6e-8 to 2.0e-7 in the VALU form).  FP64 rows are added group by group (4 U rows
+// of six components each), which keeps the chains short: 4.0e-16 against 80 bits in
+// place of 1.4e-15 for 24 to 32 columns, at the same time; the VALU form has 1.8e-16
+// to 2.5e-16, but its serial Gram pass leaves a basis 1.1e-15 to 4.6e-15 from
+// orthonormal where this one leaves 2e-16.  Bound by HBM at few right-hand sides, by
 // the FP64 matrix rate at many.  Against the VALU forms, 24 columns: 12 FP32
 // right-hand sides on 16^3x32x16 3.12 -> 1.97 ms, on 8^3x16x16 365 -> 130 us; FP64
 // on 8^3x16x16, nine 1071 us -> 27 in 397 us, four 430 -> 203 us, a Gram pass of
@@ -176,11 +180,11 @@ __global__ __launch_bounds__(256) void k_restrict_mfma(const C2* __restrict__ V,
   for (int kt = 0; kt < KT; ++kt) Vp[kt] = V + min(kt * 16 + col, a.Nv - 1) * field + chi * 6 * V5;
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) xp[nt] = x + min(r0 + nt * 8 + (col >> 1), nrhs - 1) * field + chi * 6 * V5;
-  rd4 sum[KT][NT];
+  rd4 sum[KT][NT], run[KT][NT];  // run: FP64, one group of rows, added to sum after it; FP32, all of them
 #pragma unroll
   for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) sum[kt][nt] = rd4{0, 0, 0, 0};
+    for (int nt = 0; nt < NT; ++nt) { sum[kt][nt] = rd4{0, 0, 0, 0}; run[kt][nt] = rd4{0, 0, 0, 0}; }
   struct Row { C2 v[W]; };
   auto load = [](const C2* p) {
     Row r;
@@ -226,8 +230,8 @@ __global__ __launch_bounds__(256) void k_restrict_mfma(const C2* __restrict__ V,
           for (int nt = 0; nt < NT; ++nt) {
             const C2 xv = f.xb[c][nt].v[s];
             const double b1 = im ? xv.y : xv.x, b2 = im ? -xv.x : xv.y;
-            sum[kt][nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, b1, sum[kt][nt], 0, 0, 0);
-            sum[kt][nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, b2, sum[kt][nt], 0, 0, 0);
+            run[kt][nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, b1, run[kt][nt], 0, 0, 0);
+            run[kt][nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, b2, run[kt][nt], 0, 0, 0);
           }
         }
   };
@@ -253,7 +257,22 @@ __global__ __launch_bounds__(256) void k_restrict_mfma(const C2* __restrict__ V,
       multiply(f1);
       __builtin_amdgcn_sched_barrier(0);
     }
+    if constexpr (F64) {
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          sum[kt][nt] += run[kt][nt];
+          run[kt][nt] = rd4{0, 0, 0, 0};
+        }
+    }
     i5 = next;
+  }
+  if constexpr (!F64) {
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) sum[kt][nt] = run[kt][nt];
   }
   auto row = [&](int v) { return q + 4 * v; };  // tile row of element v
   if (half == 1)

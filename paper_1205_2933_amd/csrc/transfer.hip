@@ -142,21 +142,20 @@ __global__ __launch_bounds__(256) void k_restrict(const C2* __restrict__ V, cons
 // 1.87 against 2.48 ms with FP32 tiles).  FP32 rows are widened and go through the
 // same FP64 tiles: the matrix rate is spare (FP32 tiles 1.88 ms, FP64 1.97 on that
 // case) and the sums are exact to the inputs' rounding (4.4e-8 against 64 bits,
-// 8.6e-8 to 2.0e-7 in the VALU form).  FP64 rows are added group by group (4 U rows
-// of six components each), which keeps the chains short: 4.0e-16 against 80 bits in
-// place of 1.4e-15 for 24 to 32 columns, at the same time; the VALU form has 1.8e-16
-// to 2.5e-16, but its serial Gram pass leaves a basis 1.1e-15 to 4.6e-15 from
-// orthonormal where this one leaves 2e-16.  Bound by HBM at few right-hand sides, by
-// the FP64 matrix rate at many.  Against the VALU forms, 24 columns: 12 FP32
-// right-hand sides on 16^3x32x16 3.12 -> 1.97 ms, on 8^3x16x16 365 -> 130 us; FP64
-// on 8^3x16x16, nine 1071 us -> 27 in 397 us, four 430 -> 203 us, a Gram pass of
-// the 24 basis fields 4.36 -> 0.21 ms.
+// 8.6e-8 to 2.0e-7 in the VALU form).  FP64 rows are added with a compensated sum
+// every 8 products (every 8 U with more than four tiles, whose registers allow one
+// wavefront per SIMD and leave the compensation in the open): 1.5e-16 to 1.8e-16
+// against 80 bits, where plain chains over a row group had 2.7e-16 to 3.9e-16 at the
+// same time and the VALU form has 1.7e-16 to 2.5e-16; its serial Gram pass leaves a
+// basis 1.1e-15 to 4.6e-15 from orthonormal, this one 2e-16.  Bound by HBM at few
+// right-hand sides, by the FP64 matrix rate at many.  Against the VALU forms, 24
+// columns: 12 FP32 right-hand sides on 16^3x32x16 3.12 -> 1.97 ms, on 8^3x16x16 365 ->
+// 130 us; FP64 on 8^3x16x16, nine 1071 us -> 27 in 362 us, four 430 -> 192 us.
 // Same partial layout as k_restrict.
 typedef double rd4 __attribute__((ext_vector_type(4)));
 
-
 template <class C2, int KT, int NT, int U>
-__global__ __launch_bounds__(256) void k_restrict_mfma(const C2* __restrict__ V, const C2* __restrict__ x,
+__global__ __launch_bounds__(256, sizeof(C2) == 16 && KT == 2 && NT <= 2 ? 2 : 1) void k_restrict_mfma(const C2* __restrict__ V, const C2* __restrict__ x,
                                                        double* __restrict__ partial, BlockArgs a, int nrhs) {
   using T = typename real_of<C2>::type;
   constexpr bool F64 = sizeof(T) == 8;
@@ -180,11 +179,11 @@ __global__ __launch_bounds__(256) void k_restrict_mfma(const C2* __restrict__ V,
   for (int kt = 0; kt < KT; ++kt) Vp[kt] = V + min(kt * 16 + col, a.Nv - 1) * field + chi * 6 * V5;
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) xp[nt] = x + min(r0 + nt * 8 + (col >> 1), nrhs - 1) * field + chi * 6 * V5;
-  rd4 sum[KT][NT], run[KT][NT];  // run: FP64, one group of rows, added to sum after it; FP32, all of them
-#pragma unroll
-  for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) { sum[kt][nt] = rd4{0, 0, 0, 0}; run[kt][nt] = rd4{0, 0, 0, 0}; }
+  // FP64 rows: run holds four rows of one component (8 U rows with more than four
+  // tiles) and is added to sum with the rounding carried in err (Kahan), so a chain
+  // is 8 or 16 products long.  FP32 rows, and FP64 sums that turn out not to be
+  // finite (the carried rounding of an infinity is none): run holds all rows
+  rd4 run[KT][NT], sum[F64 ? KT : 1][F64 ? NT : 1], err[F64 ? KT : 1][F64 ? NT : 1];
   struct Row { C2 v[W]; };
   auto load = [](const C2* p) {
     Row r;
@@ -218,62 +217,85 @@ __global__ __launch_bounds__(256) void k_restrict_mfma(const C2* __restrict__ V,
       for (int nt = 0; nt < NT; ++nt) f.xb[c][nt] = load(xp[nt] + (c0 + c) * V5 + i5);
     }
   };
-  auto multiply = [&](const Half& f) {
+  auto sweep = [&](auto compensated) {
+    constexpr bool KAHAN = decltype(compensated)::value;
 #pragma unroll
-    for (int c = 0; c < CH; ++c)
+    for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-      for (int s = 0; s < W; ++s)
+      for (int nt = 0; nt < NT; ++nt) {
+        run[kt][nt] = rd4{0, 0, 0, 0};
+        if constexpr (KAHAN) sum[kt][nt] = err[kt][nt] = rd4{0, 0, 0, 0};
+      }
+    auto multiply = [&](const Half& f) {
 #pragma unroll
-        for (int kt = 0; kt < KT; ++kt) {
-          const double ar = valid ? f.va[c][kt].v[s].x : (T)0, ai = valid ? f.va[c][kt].v[s].y : (T)0;
+      for (int c = 0; c < CH; ++c) {
 #pragma unroll
-          for (int nt = 0; nt < NT; ++nt) {
-            const C2 xv = f.xb[c][nt].v[s];
-            const double b1 = im ? xv.y : xv.x, b2 = im ? -xv.x : xv.y;
-            run[kt][nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, b1, run[kt][nt], 0, 0, 0);
-            run[kt][nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, b2, run[kt][nt], 0, 0, 0);
+        for (int s = 0; s < W; ++s) {
+#pragma unroll
+          for (int kt = 0; kt < KT; ++kt) {
+            const double ar = valid ? f.va[c][kt].v[s].x : (T)0, ai = valid ? f.va[c][kt].v[s].y : (T)0;
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+              const C2 xv = f.xb[c][nt].v[s];
+              const double b1 = im ? xv.y : xv.x, b2 = im ? -xv.x : xv.y;
+              run[kt][nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, b1, run[kt][nt], 0, 0, 0);
+              run[kt][nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, b2, run[kt][nt], 0, 0, 0);
+            }
           }
-        }
-  };
-  // one stage ahead: its loads are in flight during the other stage's products
-  Half f0, f1;
-  long long i5 = 0;
-  if (g0 < g1) {
-    i5 = place(g0);
-    fetch(f0, i5, 0);
-  }
-  for (int g = g0; g < g1; ++g) {
-    valid = uni || g * 4 * W + q * W < n5;
-    const long long next = place(min(g + 1, g1 - 1));
+          if constexpr (KAHAN)
+            if (KT * NT <= 4 || s == W - 1) {
 #pragma unroll
-    for (int c = 0; c < 6; c += 2 * CH) {
-      fetch(f1, i5, c + CH);
-      __builtin_amdgcn_sched_barrier(0);
-      multiply(f0);
-      __builtin_amdgcn_sched_barrier(0);
-      if (c + 2 * CH < 6) fetch(f0, i5, c + 2 * CH);
-      else fetch(f0, next, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      multiply(f1);
-      __builtin_amdgcn_sched_barrier(0);
+              for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) {
+                  const rd4 y = run[kt][nt] - err[kt][nt], t = sum[kt][nt] + y;
+                  err[kt][nt] = (t - sum[kt][nt]) - y;
+                  sum[kt][nt] = t;
+                  run[kt][nt] = rd4{0, 0, 0, 0};
+                }
+            }
+        }
+      }
+    };
+    // one stage ahead: its loads are in flight during the other stage's products
+    Half f0, f1;
+    long long i5 = 0;
+    if (g0 < g1) {
+      i5 = place(g0);
+      fetch(f0, i5, 0);
     }
-    if constexpr (F64) {
+    for (int g = g0; g < g1; ++g) {
+      valid = uni || g * 4 * W + q * W < n5;
+      const long long next = place(min(g + 1, g1 - 1));
+#pragma unroll
+      for (int c = 0; c < 6; c += 2 * CH) {
+        fetch(f1, i5, c + CH);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(f0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (c + 2 * CH < 6) fetch(f0, i5, c + 2 * CH);
+        else fetch(f0, next, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(f1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      i5 = next;
+    }
+    if constexpr (KAHAN) {
+      double check = 0.0;  // NaN when a sum is
 #pragma unroll
       for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
-          sum[kt][nt] += run[kt][nt];
-          run[kt][nt] = rd4{0, 0, 0, 0};
+          run[kt][nt] = sum[kt][nt];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) check += 0.0 * sum[kt][nt][v];
         }
+      return __any(check != check) != 0;
     }
-    i5 = next;
-  }
-  if constexpr (!F64) {
-#pragma unroll
-    for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) sum[kt][nt] = run[kt][nt];
-  }
+    return false;
+  };
+  if (sweep(std::integral_constant<bool, F64>{})) sweep(std::false_type{});
   auto row = [&](int v) { return q + 4 * v; };  // tile row of element v
   if (half == 1)
 #pragma unroll
@@ -281,7 +303,7 @@ __global__ __launch_bounds__(256) void k_restrict_mfma(const C2* __restrict__ V,
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) red[chi][kt * 16 + row(v)][nt * 16 + col] = sum[kt][nt][v];
+        for (int v = 0; v < 4; ++v) red[chi][kt * 16 + row(v)][nt * 16 + col] = run[kt][nt][v];
   __syncthreads();
   if (half == 0)
 #pragma unroll
@@ -294,7 +316,7 @@ __global__ __launch_bounds__(256) void k_restrict_mfma(const C2* __restrict__ V,
           const int k = kt * 16 + row(v);
           if (k < a.Nv && rhs < nrhs)
             partial[(((long long)rhs * a.Vc + B) * a.nsplit + split) * 4 * a.Nv + (chi * a.Nv + k) * 2 + (im ? 1 : 0)] =
-                sum[kt][nt][v] + red[chi][k][nt * 16 + col];
+                run[kt][nt][v] + red[chi][k][nt * 16 + col];
         }
       }
 }
@@ -524,23 +546,43 @@ __global__ __launch_bounds__(256) void k_gram(const double2* __restrict__ V, dou
   }
 }
 
-// coarse[(rhs * Vc + B) * n2 + row] = sum over splits, in fixed order.
+// coarse[(rhs * Vc + B) * n2 + row] = sum over splits, in fixed order: four chains
+// with their rounding carried, or one without for keep_order
 template <class C2>
 __global__ void k_restrict_finalize(const double* __restrict__ partial, C2* __restrict__ coarse,
-                                    int Vc, int n2, int nrhs, int nsplit) {
+                                    int Vc, int n2, int nrhs, int nsplit, int one_chain) {
   long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   long long tot = (long long)nrhs * Vc * n2;
   if (i >= tot) return;
   long long site = i / n2;
   int row = (int)(i - site * n2);
-  const double* p = partial + site * nsplit * 2 * n2;
-  double re = 0.0, im = 0.0;
-  for (int sp = 0; sp < nsplit; ++sp) {
-    re += p[sp * 2 * n2 + 2 * row];
-    im += p[sp * 2 * n2 + 2 * row + 1];
-  }
+  const double2* p = reinterpret_cast<const double2*>(partial) + site * nsplit * n2 + row;
   C2 v;
-  v.x = re; v.y = im;
+  if (one_chain) {
+    double re = 0.0, im = 0.0;
+    for (int sp = 0; sp < nsplit; ++sp) {
+      re += p[sp * n2].x;
+      im += p[sp * n2].y;
+    }
+    v.x = re;
+    v.y = im;
+  } else {
+    double s[4][2] = {}, err[4][2] = {};
+    for (int sp = 0; sp < nsplit; sp += 4)
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (sp + k < nsplit) {
+          const double2 a = p[(sp + k) * n2];
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            const double y = (c ? a.y : a.x) - err[k][c], t = s[k][c] + y, e = (t - s[k][c]) - y;
+            err[k][c] = e == e ? e : 0.0;  // an infinite sum stays one
+            s[k][c] = t;
+          }
+        }
+    v.x = ((s[0][0] + s[1][0]) + (s[2][0] + s[3][0])) - ((err[0][0] + err[1][0]) + (err[2][0] + err[3][0]));
+    v.y = ((s[0][1] + s[1][1]) + (s[2][1] + s[3][1])) - ((err[0][1] + err[1][1]) + (err[2][1] + err[3][1]));
+  }
   coarse[i] = v;
 }
 
@@ -841,7 +883,7 @@ void restrict_op(const C2* V, const C2* x, CC2* coarse, double* partial, const G
   MG_LAUNCH_CHECK();
   long long tot = (long long)nrhs * cg.Vc * cg.n2;
   hipLaunchKernelGGL((k_restrict_finalize<CC2>), dim3(ceil_div(tot, 256)), dim3(256), 0, st, partial,
-                     coarse, cg.Vc, cg.n2, nrhs, a.nsplit);
+                     coarse, cg.Vc, cg.n2, nrhs, a.nsplit, keep_order ? 1 : 0);
   MG_LAUNCH_CHECK();
 }
 

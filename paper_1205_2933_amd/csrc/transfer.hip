@@ -199,7 +199,7 @@ __global__ __launch_bounds__(256, sizeof(C2) == 16 && KT == 2 && NT <= 2 ? 2 : 1
     return r;
   };
   struct Half { Row va[CH][KT], xb[CH][NT]; };
-  bool valid = true;  // rows past the block count with a zero basis entry
+  bool valid = true;  // rows past the block count with x = 0 (the basis is finite)
   auto place = [&](int g) {  // this lane's row in group g
     if (uni) {
       const int jl = __builtin_amdgcn_readfirstlane(g * 4 * W / a.Ls);
@@ -233,10 +233,10 @@ __global__ __launch_bounds__(256, sizeof(C2) == 16 && KT == 2 && NT <= 2 ? 2 : 1
         for (int s = 0; s < W; ++s) {
 #pragma unroll
           for (int kt = 0; kt < KT; ++kt) {
-            const double ar = valid ? f.va[c][kt].v[s].x : (T)0, ai = valid ? f.va[c][kt].v[s].y : (T)0;
+            const double ar = f.va[c][kt].v[s].x, ai = f.va[c][kt].v[s].y;
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
-              const C2 xv = f.xb[c][nt].v[s];
+              const C2 xv = valid ? f.xb[c][nt].v[s] : cmk<C2>(0, 0);
               const double b1 = im ? xv.y : xv.x, b2 = im ? -xv.x : xv.y;
               run[kt][nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, b1, run[kt][nt], 0, 0, 0);
               run[kt][nt] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, b2, run[kt][nt], 0, 0, 0);

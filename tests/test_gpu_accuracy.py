@@ -56,3 +56,27 @@ def test_restrict_f64_rounding(cuda, L, Ls, block, nvec, n):
         want = np.stack([(np.conj(Vb[k]) * xb[r]).sum(-1) for k in range(nvec)], axis=-1)
         assert rel(got[r], want) < 2.2e-16, r
     h.close()
+
+
+# row groups that fill blocks (a sum that is not finite is taken twice) and that do
+# not (lanes past the block read its first row), FP64 and FP32
+@pytest.mark.parametrize("L,Ls,block,prec", [((4, 4, 4, 4), 16, (4, 4, 4, 4), "f64"), ((3, 2, 2, 2), 5, (3, 1, 1, 1), "f64"),
+                                             ((3, 2, 2, 2), 6, (3, 1, 1, 1), "f32"), ((4, 4, 4, 4), 8, (4, 4, 4, 4), "f32")])
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
+def test_restrict_non_finite(cuda, L, Ls, block, prec, value):
+    """One infinite entry in a block's first row makes that block's coefficients of one
+    chirality and one right-hand side infinite (never NaN), and nothing else."""
+    import paper_1205_2933_amd as mg
+    nvec = 3
+    h, V = handle_with_basis(L, Ls, block, nvec)
+    x = gaussian_fermion(L, Ls, 94, n=3)
+    x[1, 0, 0, 0, 0, 0, 0, 0] = complex(value, 0.25)
+    c = torch.empty((3, h.ncoarse), dtype=torch.complex128, device="cuda")
+    mg.mgdwf_restrict(h, dev(x), c, nrhs=3, prec=prec)
+    got = c.cpu().numpy().reshape(3, -1, 2, nvec)
+    hit = got[1, 0, 0].copy()
+    got[1, 0, 0] = 0
+    assert np.isfinite(got.view(np.float64)).all()
+    parts = hit.view(np.float64)
+    assert (np.isnan(parts) if np.isnan(value) else np.isinf(parts)).all(), hit
+    h.close()

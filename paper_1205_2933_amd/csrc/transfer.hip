@@ -143,8 +143,8 @@ __global__ __launch_bounds__(256) void k_restrict(const C2* __restrict__ V, cons
 // same FP64 tiles: the matrix rate is spare (FP32 tiles 1.88 ms, FP64 1.97 on that
 // case) and the sums are exact to the inputs' rounding (4.4e-8 against 64 bits,
 // 8.6e-8 to 2.0e-7 in the VALU form).  FP64 rows are added with a compensated sum
-// every 8 products (every 8 U with more than four tiles, whose registers allow one
-// wavefront per SIMD and leave the compensation in the open): 1.5e-16 to 1.8e-16
+// every 8 products (every 8 U with four column tiles or more than four tiles, whose
+// registers allow one wavefront per SIMD): 1.5e-16 to 1.8e-16
 // against 80 bits, where plain chains over a row group had 2.7e-16 to 3.9e-16 at the
 // same time and the VALU form has 1.7e-16 to 2.5e-16; its serial Gram pass leaves a
 // basis 1.1e-15 to 4.6e-15 from orthonormal, this one 2e-16.  Bound by HBM at few
@@ -179,10 +179,9 @@ __global__ __launch_bounds__(256, sizeof(C2) == 16 && KT == 2 && NT <= 2 ? 2 : 1
   for (int kt = 0; kt < KT; ++kt) Vp[kt] = V + min(kt * 16 + col, a.Nv - 1) * field + chi * 6 * V5;
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) xp[nt] = x + min(r0 + nt * 8 + (col >> 1), nrhs - 1) * field + chi * 6 * V5;
-  // FP64 rows: run holds four rows of one component (8 U rows with more than four
-  // tiles) and is added to sum with the rounding carried in err (Kahan), so a chain
-  // is 8 or 16 products long.  FP32 rows, and FP64 sums that turn out not to be
-  // finite (the carried rounding of an infinity is none): run holds all rows
+  // FP64 rows: run holds 8 (8 U) products and is added to sum with the rounding
+  // carried in err (Kahan).  FP32 rows, and FP64 sums that turn out not to be finite
+  // (the carried rounding of an infinity is none): run holds all rows
   rd4 run[KT][NT], sum[F64 ? KT : 1][F64 ? NT : 1], err[F64 ? KT : 1][F64 ? NT : 1];
   struct Row { C2 v[W]; };
   auto load = [](const C2* p) {
@@ -243,7 +242,7 @@ __global__ __launch_bounds__(256, sizeof(C2) == 16 && KT == 2 && NT <= 2 ? 2 : 1
             }
           }
           if constexpr (KAHAN)
-            if (KT * NT <= 4 || s == W - 1) {
+            if ((KT * NT <= 4 && NT < 4) || s == W - 1) {
 #pragma unroll
               for (int kt = 0; kt < KT; ++kt)
 #pragma unroll

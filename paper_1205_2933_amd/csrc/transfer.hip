@@ -13,6 +13,7 @@
 
 #include "mg_internal.h"
 #include "blas.h"
+#include "rules.h"
 
 namespace mgdwf {
 
@@ -31,16 +32,11 @@ struct BlockArgs {
   int nsplit;  // workgroups per coarse site in R
 };
 
-// Four workgroups per coarse site, up to 16 while there are fewer than 512 sites:
-// 2048 in all, eight per CU; 32 sites of 4096 rows with four workgroups each left
-// half the CUs idle.
-int restrict_splits(const CoarseGeometry& cg) { return std::max(4, std::min(16, 2048 / std::max(1, cg.Vc))); }
-
-BlockArgs make_args(const Geometry& g, const CoarseGeometry& cg, bool keep_order = false) {
+BlockArgs make_args(const Geometry& g, const CoarseGeometry& cg) {
   BlockArgs a;
   for (int m = 0; m < 4; ++m) { a.L[m] = g.L[m]; a.b[m] = cg.block[m]; a.Lc[m] = cg.Lc[m]; }
   a.Ls = g.Ls; a.V4 = g.V4; a.V5 = g.V5; a.Vc = cg.Vc; a.bvol = cg.bvol; a.Nv = cg.Nv;
-  a.nsplit = keep_order ? 4 : restrict_splits(cg);
+  a.nsplit = 4;
   return a;
 }
 
@@ -567,18 +563,21 @@ __global__ void k_restrict_finalize(const double* __restrict__ partial, C2* __re
     v.y = im;
   } else {
     double s[4][2] = {}, err[4][2] = {};
-    for (int sp = 0; sp < nsplit; sp += 4)
+    for (int sp = 0; sp < nsplit; sp += 4) {
+      double2 a[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) a[k] = p[min(sp + k, nsplit - 1) * n2];
 #pragma unroll
       for (int k = 0; k < 4; ++k)
         if (sp + k < nsplit) {
-          const double2 a = p[(sp + k) * n2];
 #pragma unroll
           for (int c = 0; c < 2; ++c) {
-            const double y = (c ? a.y : a.x) - err[k][c], t = s[k][c] + y, e = (t - s[k][c]) - y;
+            const double y = (c ? a[k].y : a[k].x) - err[k][c], t = s[k][c] + y, e = (t - s[k][c]) - y;
             err[k][c] = e == e ? e : 0.0;  // an infinite sum stays one
             s[k][c] = t;
           }
         }
+    }
     v.x = ((s[0][0] + s[1][0]) + (s[2][0] + s[3][0])) - ((err[0][0] + err[1][0]) + (err[2][0] + err[3][0]));
     v.y = ((s[0][1] + s[1][1]) + (s[2][1] + s[3][1])) - ((err[0][1] + err[1][1]) + (err[2][1] + err[3][1]));
   }
@@ -838,13 +837,13 @@ __global__ __launch_bounds__(256) void k_apply_rinv(double2* __restrict__ V, con
 // ---------------------------------------------------------------- host API
 
 size_t restrict_partial_doubles(const CoarseGeometry& cg, int nrhs) {
-  return (size_t)nrhs * cg.Vc * restrict_splits(cg) * 2 * cg.n2;
+  return (size_t)nrhs * cg.Vc * restrict_splits(cg.Vc) * 2 * cg.n2;  // the most any rule gives
 }
 
 template <class C2, class CC2>
 void restrict_op(const C2* V, const C2* x, CC2* coarse, double* partial, const Geometry& g,
                  const CoarseGeometry& cg, int nrhs, hipStream_t st, bool keep_order) {
-  BlockArgs a = make_args(g, cg, keep_order);
+  BlockArgs a = make_args(g, cg);
   constexpr bool f64 = sizeof(typename real_of<C2>::type) == 8;
   // the FP32 multi-RHS kernels read s-pairs: Ls even keeps every pair inside one site
   if (keep_order && nrhs >= 2 && (f64 || g.Ls % 2 == 0)) {
@@ -862,6 +861,7 @@ void restrict_op(const C2* V, const C2* x, CC2* coarse, double* partial, const G
                          partial, a, nrhs);
   } else if (nrhs >= 2 && cg.Nv <= 32 && (f64 || g.Ls % 2 == 0)) {
     const int nt = std::min(4, ceil_div(nrhs, 8));
+    a.nsplit = restrict_splits(cg.Vc);
     const dim3 grid(cg.Vc * a.nsplit, ceil_div(nrhs, 8 * nt));
     const bool wide = g.Ls % (f64 ? 2 : 4) == 0;  // 32 bytes per lane: a group of four lanes reads whole 128-byte lines
 #define MG_RM(KT, NT) \
@@ -877,6 +877,7 @@ void restrict_op(const C2* V, const C2* x, CC2* coarse, double* partial, const G
 #undef MG_RMN
 #undef MG_RM
   } else {
+    if (!keep_order) a.nsplit = restrict_splits_general(cg.Vc, cg.bvol * g.Ls, nrhs, f64);
     hipLaunchKernelGGL((k_restrict<C2>), dim3(cg.Vc * a.nsplit, nrhs), dim3(256), 0, st, V, x, partial, a);
   }
   MG_LAUNCH_CHECK();

@@ -1,0 +1,42 @@
+"""The launch rules that follow from sizes alone (csrc/rules.h), over their ranges,
+from a host program compiled here."""
+import subprocess
+from pathlib import Path
+
+import pytest
+
+ROOT = Path(__file__).resolve().parents[1]
+
+
+def evaluate(tmp_path, expr, calls):
+    """expr, a C++ expression in q[0], q[1], ..., for every tuple of calls."""
+    src = tmp_path / "rules.cpp"
+    src.write_text('#include "rules.h"\n#include <cstdio>\nusing namespace mgdwf;\nint main() {\n'
+                   '  long long q[8];\n  while (scanf("%lld %lld %lld %lld", q, q + 1, q + 2, q + 3) == 4)\n'
+                   f'    printf("%lld\\n", (long long)({expr}));\n}}\n')
+    exe = tmp_path / "rules"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", str(ROOT / "paper_1205_2933_amd" / "csrc"), str(src), "-o", str(exe)],
+                   check=True)
+    pad = lambda c: " ".join(str(int(v)) for v in (tuple(c) + (0, 0, 0, 0))[:4])
+    out = subprocess.run([str(exe)], input="\n".join(map(pad, calls)), capture_output=True, text=True, check=True)
+    return [int(v) for v in out.stdout.split()]
+
+
+SITES = sorted({1, 2, 9, 16, 32, 48, 85, 86, 96, 108, 127, 128, 129, 144, 162, 170, 171, 192, 240, 255, 256, 257, 512,
+                1024, 2592, 4096, 65536})
+
+
+def test_restriction_splits(tmp_path):
+    """Every split has rows of its own beyond the first four, the workspace holds any count,
+    and more than four splits stay within two workgroups per CU (eight in FP64)."""
+    calls = [(vc, rows, n, f64) for vc in SITES for rows in (1, 80, 96, 255, 256, 1024, 1279, 1280, 1792, 4096, 5775, 65536)
+             for n in (1, 2, 3, 12, 300) for f64 in (0, 1)]
+    got = evaluate(tmp_path, "restrict_splits_general(q[0], q[1], q[2], q[3])", calls)
+    most = evaluate(tmp_path, "restrict_splits(q[0])", calls)
+    for (vc, rows, n, f64), s, m in zip(calls, got, most):
+        assert 4 <= s <= m <= 16, (vc, rows, n, f64, s, m)
+        if s > 4:
+            assert s * 256 <= rows and vc * n * s <= (2048 if f64 else 512), (vc, rows, n, f64, s)
+    # blocks of few rows keep four (they took up to 3.6 times as long with 16)
+    assert set(evaluate(tmp_path, "restrict_splits_general(q[0], q[1], q[2], q[3])",
+                        [(16, 80, 12, 0), (256, 256, 1, 1), (256, 96, 1, 0), (16, 128, 1, 1)])) == {4}

@@ -1739,7 +1739,7 @@ __global__ __launch_bounds__(TX * TY * TZ * 8, TX * TY * TZ >= 64 ? 1 : 2) void 
 // neighbours and slice t + 1 are loaded.  CANON: fields in the canonical order
 // (the 12 components of a site together, 192 bytes per lane).
 // Bound by L2 reads and load latency (two wavefronts per SIMD, 256 VGPRs).
-// 16^3x32x16: 281 us for one field and 3.17 ms for 12 (3.1 TB/s), 4.36 ms for 12
+// 16^3x32x16: 277 us for one field and 3.18 ms for 12 (3.1 TB/s), 4.29 ms for 12
 // canonical ones, against 405 us, 4.85 ms and 6.65 ms with k_dslash, which loads
 // every neighbour and link per lane.  A 4 x 2 x 2 tile with two workgroups per
 // CU: 278 us, 3.35 ms, 4.91 ms.
@@ -1941,15 +1941,9 @@ __global__ __launch_bounds__(TX * TY * TZ * 16, 2) void k_dslash_dx(const double
       ((lds_d2w_t)(void*)sP)[k * cst + me] = nd2{p.v[k / 3][k % 3].x, p.v[k / 3][k % 3].y};
     __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the slice is written; nothing else needs to land
     __builtin_amdgcn_s_barrier();
-    // own terms (scaled by -2: the sum is halved at the end), backward t-hop
+    // backward t-hop
 #pragma unroll
-    for (int k = 0; k < 12; ++k) {
-      const bool up = k / 3 == up0 || k / 3 == up0 + 1;
-      const nd2 v = lP[k * cst + (up ? jq : jm)];
-      double2 r = cscale(p.v[k / 3][k % 3], dg);
-      r = cadd(r, cscale(make_double2(v.x, v.y), up ? cup : cdn));
-      acc.v[k / 3][k % 3] = cscale(r, -2.0);
-    }
+    for (int k = 0; k < 12; ++k) acc.v[k / 3][k % 3] = make_double2(0.0, 0.0);
     mul_link<true>(U, hp, u, 1.0f);
     accumulate<3, EB>(acc, u);
     project<3, EB>(p, hp);
@@ -1974,7 +1968,12 @@ __global__ __launch_bounds__(TX * TY * TZ * 16, 2) void k_dslash_dx(const double
     const unsigned o5 = off64<CANON>(x4 * Ls + s);
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
-      double2 r = cscale(acc.v[k / 3][k % 3], -0.5);
+      // own terms last, as in k_dslash: with them first every hop is added to a
+      // larger number (1.5e-16 against 80 bits in place of 1.0e-16)
+      const bool up = k / 3 == up0 || k / 3 == up0 + 1;
+      const nd2 own = lP[k * cst + me], v = lP[k * cst + (up ? jq : jm)];
+      double2 r = cadd(cscale(make_double2(own.x, own.y), dg), cscale(acc.v[k / 3][k % 3], -0.5));
+      r = cadd(r, cscale(make_double2(v.x, v.y), up ? cup : cdn));
       if (MODE == 1) {
         const nd2 bb = __builtin_nontemporal_load((gd2_t)(sbase(bb0, cs, k) + o5));
         r = make_double2(bb.x - r.x, bb.y - r.y);

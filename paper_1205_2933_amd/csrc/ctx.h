@@ -36,12 +36,17 @@ struct mgdwf_ctx {
   mgdwf::CoarseGeometry cg2{};   // level-2 lattice: Lc = blocks, Vc, Nv = Nv2, n2, block = coarse sites per block
   mgdwf::DevBuf W2null, W2_64, W2_32, Acc64, Acc32;
 
-  // Sums in one fixed order that no lattice-dependent kernel choice changes: during
-  // a squared setup (and its builds) and a squared mixed-precision solve (KeepOrder).
+  // On during a squared setup (with its builds), mgdwf_setup_level2 and a squared
+  // mixed-precision solve (KeepOrder): they run the kernels, or others with the same
+  // order of sums, that the library first had for them, so that their results repeat
+  // bit for bit from one version of the other kernels to the next.  Nothing more: the
+  // kernel still follows the lattice, the batch and the chosen tiling, as elsewhere.
   // Such a solve stops at a residual that leaves 1e-9 to 5e-9 of error in D's lowest
   // modes, and a single rounding redraws it: with the right-hand sides scaled by 1 +
   // 1e-15 the solutions move by 9e-10 to 5e-9 and the outer iterations from 96 to 87
   // (8^3x16x16, m_f 0.001, residual 1e-10).  The 9-point solves move by 1e-10.
+  // Off: FP64 solves and cycles, mgdwf_apply_vcycle and single operator calls, so a
+  // cycle as a call differs in rounding from the same cycle inside a solve.
   bool keep_order = false;
 
   mgdwf_mg_params mp{};

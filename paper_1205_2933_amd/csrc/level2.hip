@@ -294,8 +294,8 @@ template void prolong2<float2>(const float2*, const float2*, float2*, bool, cons
                                const CoarseGeometry&, int, hipStream_t);
 
 void build_level2_op(const double2* Ac, const double2* W, double2* Acc, double2* probes, double2* applied,
-                     double2* rr, const CoarseGeometry& cg, const CoarseGeometry& c2, hipStream_t st) {
-  build_galerkin_op([&](const double2* x, double2* y, int n) { sq_apply64(Ac, x, y, cg, n, st); }, W, Acc, probes,
+                     double2* rr, const CoarseGeometry& cg, const CoarseGeometry& c2, bool keep_order, hipStream_t st) {
+  build_galerkin_op([&](const double2* x, double2* y, int n) { sq_apply64(Ac, x, y, cg, n, st, keep_order); }, W, Acc, probes,
                     applied, rr, cg, c2, st);
 }
 

@@ -376,11 +376,11 @@ struct TwoLevel {
 // the coarse correction recomputed with N.  M approximates N^-1 D^+ = D^-1,
 // so it preconditions the same flexible GCR on D x = b.
 inline void sq_op(mgdwf_ctx* c, const double2* x, double2* y, int nrhs) {
-  sq_apply64(c->Asq.m64.as<double2>(), x, y, c->cg, nrhs, c->st);
+  sq_apply64(c->Asq.m64.as<double2>(), x, y, c->cg, nrhs, c->st, c->keep_order);
   c->coarse_applies += 1;
 }
 inline void sq_op(mgdwf_ctx* c, const float2* x, float2* y, int nrhs) {
-  sq_apply32(c->Asq.m32.as<float2>(), x, y, c->cg, nrhs, c->st);
+  sq_apply32(c->Asq.m32.as<float2>(), x, y, c->cg, nrhs, c->st, c->keep_order);
   c->coarse_applies += 1;
 }
 
@@ -997,6 +997,7 @@ static void require(bool cond, mgdwf_status code, const char* msg) {
 void setup_level2(mgdwf_ctx* c, const mgdwf_level2_params& p, const double2* W0, double* null_residual) {
   require(c->have_coarse && c->coarse_kind == 1, MGDWF_ERR_STATE,
        "the third level needs the squared coarse operator (a squared setup or mgdwf_build_coarse_squared)");
+  const KeepOrder keep(c, true);
   const CoarseGeometry& cg = c->cg;
   CoarseGeometry c2{};
   c2.planar = cg.planar;
@@ -1031,14 +1032,14 @@ void setup_level2(mgdwf_ctx* c, const mgdwf_level2_params& p, const double2* W0,
   double2* q = c->buf<double2>("l2s_q", n * nc);
   const double2* Ac = c->Asq.m64.as<double2>();
   if (p.null_iters > 0) {  // CG on A_c w = 0 from w: r = -A_c w, p = r
-    sq_apply64(Ac, w, q, cg, n, c->st);
+    sq_apply64(Ac, w, q, cg, n, c->st, c->keep_order);
     zero<double2>(r, n * nc, c->st);
     sub_into<double2>(r, r, q, n * nc, c->st);
     copy(c, r, pv, n * nc);
     norm_into<double2>(c, r, nullptr, nc, n, S_CRR_A);
     int cur = S_CRR_A, nxt = S_CRR_B;
     for (int it = 0; it < p.null_iters; ++it) {
-      sq_apply64(Ac, pv, q, cg, n, c->st);                                   // q = A_c p
+      sq_apply64(Ac, pv, q, cg, n, c->st, c->keep_order);                    // q = A_c p
       norm_into<double2>(c, pv, q, nc, n, S_CPQ);                            // <p, q>
       mr_update<double2>(w, r, pv, q, nc, n, sl, cur, S_CPQ + 1, false, vpart, c->st);  // w += a p, r -= a q
       finalize_rhs(vpart, vec_blocks(nc), 1, sl, nxt, n, c->st);
@@ -1050,7 +1051,7 @@ void setup_level2(mgdwf_ctx* c, const mgdwf_level2_params& p, const double2* W0,
   norm_into<double2>(c, w, nullptr, nc, n, S_TMP);
   scale_by_rsqrt_slot<double2>(w, w, nc, n, sl, S_TMP, c->st);
   if (null_residual) {  // median |A_c w| for the unit vectors
-    sq_apply64(Ac, w, q, cg, n, c->st);
+    sq_apply64(Ac, w, q, cg, n, c->st, c->keep_order);
     norm_into<double2>(c, q, nullptr, nc, n, S_TMP);
     std::vector<double> h = read_slots(c, n);
     std::vector<double> v(n);
@@ -1068,7 +1069,7 @@ void setup_level2(mgdwf_ctx* c, const mgdwf_level2_params& p, const double2* W0,
   double2* probes = c->buf<double2>("l2s_probe", (size_t)c2.n2 * nc);
   double2* applied = c->buf<double2>("l2s_applied", (size_t)c2.n2 * nc);
   double2* rr = c->buf<double2>("l2s_rr", (size_t)c2.n2 * c2.Vc * c2.n2);
-  build_level2_op(Ac, c->W2_64.as<double2>(), c->Acc64.as<double2>(), probes, applied, rr, cg, c2, c->st);
+  build_level2_op(Ac, c->W2_64.as<double2>(), c->Acc64.as<double2>(), probes, applied, rr, cg, c2, c->keep_order, c->st);
   c->coarse_applies += c2.Vc;
   c->Acc32.alloc(sq_coarse_entries(c2) * sizeof(float2));
   sq_to_f32(c->Acc64.as<double2>(), c->Acc32.as<float2>(), c2, c->st);

@@ -316,7 +316,7 @@ __global__ __launch_bounds__(256, sizeof(C2) == 16 && KT == 2 && NT <= 2 ? 2 : 1
       }
 }
 
-// ---- restriction and Gram sums in one fixed order (keep_order in ctx.h)
+// ---- restriction and Gram sums in the order that keep_order keeps (ctx.h)
 //
 // Multi-RHS restriction: as k_restrict, for RG right-hand sides per workgroup
 // (blockIdx.y picks the group).  A thread keeps the rows of its RG right-hand

@@ -181,6 +181,7 @@ void build_galerkin_op(const std::function<void(const double2*, double2*, int)>&
 // A_cc = R2 A_c P2 into the 33-offset form (Vcc x 33 column-major 2Nv2 blocks);
 // probes and applied: 2 Nv2 coarse vectors each, rr: 2 Nv2 level-2 vectors
 void build_level2_op(const double2* Ac, const double2* W, double2* Acc, double2* probes, double2* applied,
-                     double2* rr, const CoarseGeometry& cg, const CoarseGeometry& c2, hipStream_t st);
+                     double2* rr, const CoarseGeometry& cg, const CoarseGeometry& c2, bool keep_order,
+                     hipStream_t st);
 
 }  // namespace mgdwf

@@ -526,7 +526,9 @@ mgdwf_status mgdwf_set_tiling(mgdwf_handle h, int32_t id);
 /* Launch kernel `k` `iters` times back to back on the handle's stream on
  * internal buffers and return the mean time per launch in *ms, measured with
  * HIP events recorded on that stream.  On a 2D handle the kernels are the 2D
- * model's (its Dslash, R, P and A_c). */
+ * model's (its Dslash, R, P and A_c).  FP32 A_c: while the handle's parameters are a
+ * squared multigrid with an FP32 fine level, the kernel that such a solve runs;
+ * otherwise that of mgdwf_apply_coarse. */
 mgdwf_status mgdwf_time_kernel(mgdwf_handle h, mgdwf_kernel k, mgdwf_prec prec, int32_t nrhs,
                                int32_t iters, double* ms);
 

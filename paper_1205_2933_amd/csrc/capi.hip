@@ -957,7 +957,7 @@ mgdwf_status mgdwf_time_kernel(mgdwf_handle h, mgdwf_kernel k, mgdwf_prec prec, 
                          h->st);
             else
               sq_apply32(h->Asq.m32.as<float2>(), h->buf<float2>("t_c32", nc), h->buf<float2>("t_d32", nc), h->cg,
-                         nrhs, h->st);
+                         nrhs, h->st, h->have_params && h->mp.squared && h->mp.fine_prec == MGDWF_F32);
           } else if (k == MGDWF_K_COARSE) {
             if (prec == MGDWF_F64)
               coarse_apply64(h->Dc, h->buf<double2>("t_c", nc), h->buf<double2>("t_d", nc), h->cg, nrhs, h->st);

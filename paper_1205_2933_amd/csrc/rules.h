@@ -22,4 +22,23 @@ inline int restrict_splits_general(int Vc, int rows, int nrhs, bool f64) {
   return std::max(4, std::min(want, std::min(16, rows / 256)));
 }
 
+// Right-hand sides per workgroup (1 to 4) of the ordered squared apply, 0 where the
+// general kernel, which has the same bits and reads the matrix once per 16, is the
+// faster one.  A workgroup per site and group; as many groups as fit into the rounds of
+// 256 workgroups that groups of four take anyway, of two and more right-hand sides
+// where a site's groups land on different XCDs (Vc no multiple of 8) and each reads the
+// matrix for itself.  Rounds cost 14 to 25 us at 48 dof (one to four right-hand sides),
+// passes of the general kernel 45 to 75, and beyond 160 sites the matrix (0.1 GB) comes
+// from HBM once per group: 512 sites, 12 right-hand sides 144 us in the general kernel,
+// 180 in groups of four, 234 of eight; 128 sites, 12: 37 us in groups of three, 61 in
+// the general kernel.  16 dof on 1024 sites and more keep the groups (12: 78 against 95),
+// 64 dof there do not (one right-hand side: 194 against 184).
+inline int sq_ordered_group(long long Vc, int n2, int nrhs) {
+  const long long fewest = (nrhs + 3) / 4, rounds = (Vc * fewest + 255) / 256;
+  if (nrhs > 4 && !(n2 == 16 && Vc >= 1024) && (Vc > (Vc % 8 != 0 ? 128 : 160) || rounds >= 3 * ((nrhs + 15) / 16))) return 0;
+  if (nrhs == 1 && n2 == 64 && Vc >= 1024) return 0;
+  const long long groups = std::max(fewest, 256 * rounds / Vc), least = Vc > 32 && Vc % 8 != 0 ? 2 : 1;
+  return (int)std::min<long long>(nrhs, std::max(least, (nrhs + groups - 1) / groups));
+}
+
 }  // namespace mgdwf

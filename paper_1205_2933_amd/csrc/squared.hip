@@ -28,6 +28,7 @@
 
 #include "mg_internal.h"
 #include "blas.h"
+#include "rules.h"
 #include "vecops.h"
 
 namespace mgdwf {
@@ -213,7 +214,9 @@ __global__ __launch_bounds__(576) void k_sq_apply(const MC2* __restrict__ M, con
 // as above, but blockIdx.y picks NR right-hand sides, the vector entries, the same
 // for a whole wavefront, come as scalar loads (no panel, no barrier before the final
 // sum) and KC columns are in flight ahead of those being multiplied.  Bound by load
-// latency at few sites, by the bytes of M at many.
+// latency at few sites (32 sites x 48 dof, 4 right-hand sides: 14.4 us, 25.4 in the
+// kernel above), by the bytes of M at many (512, one: 51 us, 6.2 TB/s); which of the two
+// runs: sq_ordered_group.
 template <int N2, int NR>
 __global__ __launch_bounds__(576) void k_sq_ordered(const float2* __restrict__ M, const float2* __restrict__ x,
                                                     float2* __restrict__ y, SqArgs a, int nrhs) {
@@ -663,16 +666,16 @@ void sq_apply64(const double2* Ac, const double2* x, double2* y, const CoarseGeo
 
 static bool sq_ordered_launch(const float2* A, const float2* x, float2* y, const SqArgs& a, const CoarseGeometry& cg, int nrhs,
                               hipStream_t st) {
+  const int nr = sq_ordered_group(cg.Vc, cg.n2, nrhs);
+  if (nr == 0) return false;
   const bool done = with_sq_n2(cg.n2, [&](auto N) {
     constexpr int N2 = decltype(N)::value;
-    const dim3 blk(576);
-#define MG_SQO(NR) \
-  hipLaunchKernelGGL((k_sq_ordered<N2, NR>), dim3(cg.Vc, ceil_div(nrhs, NR)), blk, 0, st, A, x, y, a, nrhs)
-    const int nr = ceil_div(nrhs * cg.Vc, 256);  // right-hand sides a workgroup takes with one for every CU
-    if (nr <= 1) MG_SQO(1);
-    else if (nr <= 2) MG_SQO(2);
-    else if (nr <= 4) MG_SQO(4);
-    else MG_SQO(8);
+    const dim3 grid(cg.Vc, ceil_div(nrhs, nr)), blk(576);
+#define MG_SQO(NR) hipLaunchKernelGGL((k_sq_ordered<N2, NR>), grid, blk, 0, st, A, x, y, a, nrhs)
+    if (nr == 1) MG_SQO(1);
+    else if (nr == 2) MG_SQO(2);
+    else if (nr == 3) MG_SQO(3);
+    else MG_SQO(4);
 #undef MG_SQO
   });
   if (done) MG_LAUNCH_CHECK();

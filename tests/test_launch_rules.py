@@ -40,3 +40,20 @@ def test_restriction_splits(tmp_path):
     # blocks of few rows keep four (they took up to 3.6 times as long with 16)
     assert set(evaluate(tmp_path, "restrict_splits_general(q[0], q[1], q[2], q[3])",
                         [(16, 80, 12, 0), (256, 256, 1, 1), (256, 96, 1, 0), (16, 128, 1, 1)])) == {4}
+
+
+def test_ordered_apply_groups(tmp_path):
+    """No workgroup without right-hand sides, and where the matrix is too large for the
+    caches one pass over it per four right-hand sides at most, or the general kernel (0)."""
+    calls = [(vc, n2, n) for vc in SITES for n2 in (16, 32, 48, 64) for n in range(1, 41)]
+    for (vc, n2, n), g in zip(calls, evaluate(tmp_path, "sq_ordered_group(q[0], (int)q[1], (int)q[2])", calls)):
+        assert 0 <= g <= min(n, 4), (vc, n2, n, g)
+        if g:
+            groups = -(-n // g)
+            assert (groups - 1) * g < n, (vc, n2, n, g)
+            if vc >= 256:
+                assert groups == -(-n // 4), (vc, n2, n, g)  # one right-hand side is not worked on twice, nor four in two
+        if n <= 4:
+            assert g or (n, n2) == (1, 64), (vc, n2, n)
+        elif vc > 160 and not (n2 == 16 and vc >= 1024):
+            assert g == 0, (vc, n2, n)

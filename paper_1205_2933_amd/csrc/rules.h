@@ -41,4 +41,20 @@ inline int sq_ordered_group(long long Vc, int n2, int nrhs) {
   return (int)std::min<long long>(nrhs, std::max(least, (nrhs + groups - 1) / groups));
 }
 
+// Whether the squared MFMA kernels give the 16-row tiles of a site to different
+// workgroups (16 rows each) or all to one; sites: coarse sites times groups of eight
+// right-hand sides.  The split form's rounds of 256 workgroups are shorter but more:
+// it takes one round of them, and two where a round of whole sites costs more than
+// two of its own (64 dof except in an FP32 CG step, 48 dof in the FP32 product); beyond,
+// a nearly empty last round decides.  us, split / whole sites, FP64 and FP32, one
+// right-hand side: 48 dof, 80 sites 18.5 / 26.6 and 11.4 / 19.9, 128 sites 30.0 / 28.3
+// and 18.1 / 20.7, 192 sites 45.1 / 36.2 and 25.8 / 23.5; 64 dof, 128 sites 47.1 / 50.2
+// and 25.2 / 33.0, 162 sites 73.4 / 60.7 and 33.2 / 34.1; 32 dof, 128 sites 14.0 / 16.7 and
+// 7.8 / 10.9, 144 sites 21.0 / 17.7 and 12.7 / 11.2; 12 right-hand sides, 48 dof on 120
+// sites 50.4 / 29.3 and 29.1 / 21.8.
+inline bool sq_split_rows(long long sites, int row_tiles, bool f64, bool cg_step) {
+  const bool two = row_tiles >= 4 ? f64 || !cg_step : row_tiles == 3 && !f64 && !cg_step;
+  return sites * row_tiles <= (two ? 512 : 256);
+}
+
 }  // namespace mgdwf

@@ -565,15 +565,10 @@ static bool sq_mfma_launch(const C2* A, O2* y, const SqStep<C2>& q, const Coarse
     constexpr int MT = N2 / 16;
     const int groups = ceil_div(nrhs, 8);
     const dim3 blk(SQW * 64);
-    // A site's rows together where sites and groups of right-hand sides make a
-    // workgroup for every CU (whole blocks stream in address order), else a
-    // workgroup per 16 rows.  48 dof, split / together, FP64 and FP32 us: 32 sites,
-    // 4 right-hand sides 13.9 / 26.4 and 9.8 / 20.1; 128 sites, 8: 30.9 / 28.9 and
-    // 21.1 / 21.4, 12: 52.4 / 29.9 and 29.1 / 22.2; 512 sites, 4: 124 / 112 and 75.5 /
-    // 60.3.  FP32 takes 16 right-hand sides per pass over the matrix on 256 sites
-    // or more (512, 12: 82 us against 113; 128, 12: 31 against 22); a CG step has no
-    // registers for it.
-    if (groups * cg.Vc < 256) {
+    // FP32 takes 16 right-hand sides per pass over the matrix on 256 sites or more (48
+    // dof, 512 sites, 12: 82 us against 113; 128, 12: 31 against 22); a CG step has no
+    // registers for it
+    if (sq_split_rows((long long)groups * cg.Vc, MT, std::is_same<C2, double2>::value, CG)) {
       hipLaunchKernelGGL((k_sq_mfma<C2, O2, N2, 1, 1, CG>), dim3(cg.Vc, MT * groups), blk, 0, st, A, y, q, a, nrhs);
       return;
     }

@@ -57,3 +57,15 @@ def test_ordered_apply_groups(tmp_path):
             assert g or (n, n2) == (1, 64), (vc, n2, n)
         elif vc > 160 and not (n2 == 16 and vc >= 1024):
             assert g == 0, (vc, n2, n)
+
+
+def test_row_split_rounds(tmp_path):
+    """The split form takes at most two rounds of 256 workgroups, and only where the sites
+    alone are no full round."""
+    calls = [(v, mt, f64, cg) for v in SITES for mt in (2, 3, 4) for f64 in (0, 1) for cg in (0, 1)]
+    for (v, mt, f64, cg), split in zip(calls, evaluate(tmp_path, "sq_split_rows(q[0], (int)q[1], q[2], q[3])", calls)):
+        rounds = -(-v * mt // 256)
+        assert not split or (rounds <= 2 and v < 256), (v, mt, f64, cg)
+        assert split or rounds > 1, (v, mt, f64, cg)
+    # 162 sites x 64 dof, one right-hand side: 73 us split, 61 with whole sites
+    assert evaluate(tmp_path, "sq_split_rows(q[0], (int)q[1], q[2], q[3])", [(162, 4, 1, 0), (162, 4, 0, 0)]) == [0, 0]

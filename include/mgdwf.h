@@ -211,7 +211,8 @@ mgdwf_status mgdwf_destroy(mgdwf_handle h);
 const char* mgdwf_last_error(mgdwf_handle h);
 
 /* Copy the gauge field (canonical complex128, device) into the internal
- * FP64 and FP32 link layouts.  Invalidates any basis / coarse operator. */
+ * FP64 and FP32 link layouts (with an antiperiodic direction the FP64 links are
+ * held twice, 576 bytes per 4D site more).  Invalidates any basis / coarse operator. */
 mgdwf_status mgdwf_set_gauge(mgdwf_handle h, const double* U);
 
 /* ---- fine operator (step a1) ------------------------------------------ */
@@ -251,7 +252,9 @@ mgdwf_status mgdwf_prolong(mgdwf_handle h, const double* coarse, double* fine, i
 /* ---- coarse operator (steps a6, a7): Sec. 2 step 3, Sec. 4 ------------ */
 
 /* Build D_c = R D P as the 9-point stencil of dense 2Nv x 2Nv blocks (FP64),
- * plus its FP32, FP16 and BF16 copies with one scale per block. */
+ * plus its FP32, FP16 and BF16 copies with one scale per block.  While it runs it
+ * holds 27 FP64 fields, or 9 where 27 would pass 16 GB or half of the free memory
+ * (the result is the same). */
 mgdwf_status mgdwf_build_coarse(mgdwf_handle h);
 /* Build the squared operator's coarse operator A_c = P^+ D^+ D P (Sec. 3,
  * Sec. 4) on the installed basis: a stencil over the 33 offsets o = self,

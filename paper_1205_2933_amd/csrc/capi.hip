@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "ctx.h"
+#include "rules.h"
 #include "solver.h"
 
 using namespace mgdwf;
@@ -187,16 +188,19 @@ void build_coarse(mgdwf_ctx* c) {
   const CoarseGeometry& cg = c->cg;
   const long long ndc = (long long)cg.Vc * 9 * cg.n2 * cg.n2;
   c->Dc.m64.alloc(ndc * sizeof(double2));
-  const int nb = coarse_build_columns(c->g);
+  size_t free_bytes = 0, total_bytes = 0;
+  MG_HIP(hipMemGetInfo(&free_bytes, &total_bytes));
+  const int nb = coarse_build_columns((double)c->fine_len() * sizeof(double2), (double)free_bytes);
   double2* work9 = c->buf<double2>("dc_work9", 9 * nb * c->fine_len());
   double2* cwork = c->buf<double2>("dc_cwork", 9LL * nb * cg.Vc * cg.n2);
   double* partial = c->buf<double>("dc_partial", restrict_partial_doubles(cg, 9 * nb));
   build_coarse_op(c->V64.as<double2>(), c->U64.as<double2>(), c->Dc.m64.as<double2>(), work9, cwork, partial, c->g,
-                  cg, c->M5, c->mf, c->st);
+                  cg, c->M5, c->mf, nb, c->st);
+  // the build's fields are large: give them back before the copies are made
+  MG_HIP(hipStreamSynchronize(c->st));
+  c->ws.erase("dc_work9");
   finish_coarse_op(c->Dc, c->DcH, cg, c->st);
   MG_HIP(hipStreamSynchronize(c->st));
-  // the build workspaces are large; give them back
-  c->ws.erase("dc_work9");
   c->coarse_kind = 0;
   c->have_l2 = false;
   c->have_coarse = true;

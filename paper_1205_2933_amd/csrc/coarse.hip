@@ -762,25 +762,19 @@ __global__ __launch_bounds__(576) void k_cgne_persistent(PersistArgs q) {
 
 }  // namespace
 
-// Columns of a coarse build restricted together: the restriction reads the basis
-// once per 32 right-hand sides, three columns' nine pieces fill 27; one column
-// at a time where 27 FP64 fields would pass 16 GB.
-int coarse_build_columns(const Geometry& g) { return 27.0 * 12 * 16 * g.V5 <= 16e9 ? 3 : 1; }
-
-// Build the FP64 coarse operator.  Vhat: orthonormal basis (Nv FP64 fields);
-// with nb = coarse_build_columns: work9: 9 nb fine FP64 fields; cwork: 9 nb Vc n2
-// complex; partial: restriction scratch for 9 nb right-hand sides.
+// Build the FP64 coarse operator, nb = `columns` columns at a time (the same bits for
+// any).  Vhat: orthonormal basis (Nv FP64 fields); work9: 9 nb fine FP64 fields; cwork:
+// 9 nb Vc n2 complex; partial: restriction scratch for 9 nb right-hand sides.
 void build_coarse_op(const double2* Vhat, const double2* gauge, double2* Dc, double2* work9, double2* cwork,
                      double* partial, const Geometry& g, const CoarseGeometry& cg, double M5, double mf,
-                     hipStream_t st) {
+                     int columns, hipStream_t st) {
   const long long field = 12LL * g.V5;
-  const int nbmax = coarse_build_columns(g);
-  for (int j0 = 0; j0 < cg.n2; j0 += nbmax) {
-    const int nb = std::min(nbmax, cg.n2 - j0);
+  for (int j0 = 0; j0 < cg.n2; j0 += columns) {
+    const int nb = std::min(columns, cg.n2 - j0);
     for (int q = 0; q < nb; ++q)  // column j = chi * Nv + k
       dslash_split(Vhat + (j0 + q) % cg.Nv * field, work9 + q * 9 * field, gauge, g, cg.block, M5, mf,
                    (j0 + q) / cg.Nv, st);
-    restrict_op<double2, double2>(Vhat, work9, cwork, partial, g, cg, 9 * nb, st);
+    restrict_op<double2, double2>(Vhat, work9, cwork, partial, g, cg, 9 * nb, st, false, 4);
     long long tot = 9LL * cg.Vc * cg.n2 * nb;
     hipLaunchKernelGGL(k_scatter_columns, dim3(ceil_div(tot, 256)), dim3(256), 0, st, cwork, Dc, cg.Vc, cg.n2, j0, nb);
     MG_LAUNCH_CHECK();

@@ -57,4 +57,13 @@ inline bool sq_split_rows(long long sites, int row_tiles, bool f64, bool cg_step
   return sites * row_tiles <= (two ? 512 : 256);
 }
 
+// Columns of a coarse build restricted together: the restriction reads the basis once
+// per 32 right-hand sides, and three columns' nine pieces fill 27 (8^3x16x16, 24 columns:
+// 8.8 ms against 17.7).  One at a time, as many fields as the build's steps need at
+// least, where the 27 FP64 fields would pass 16 GB or take more than half of the
+// memory that is free.
+inline int coarse_build_columns(double field_bytes, double free_bytes) {
+  return 27 * field_bytes <= std::min(16e9, 0.5 * free_bytes) ? 3 : 1;
+}
+
 }  // namespace mgdwf

@@ -842,7 +842,7 @@ size_t restrict_partial_doubles(const CoarseGeometry& cg, int nrhs) {
 
 template <class C2, class CC2>
 void restrict_op(const C2* V, const C2* x, CC2* coarse, double* partial, const Geometry& g,
-                 const CoarseGeometry& cg, int nrhs, hipStream_t st, bool keep_order) {
+                 const CoarseGeometry& cg, int nrhs, hipStream_t st, bool keep_order, int column_tiles) {
   BlockArgs a = make_args(g, cg);
   constexpr bool f64 = sizeof(typename real_of<C2>::type) == 8;
   // the FP32 multi-RHS kernels read s-pairs: Ls even keeps every pair inside one site
@@ -860,7 +860,7 @@ void restrict_op(const C2* V, const C2* x, CC2* coarse, double* partial, const G
       hipLaunchKernelGGL((k_restrict_mr<C2, RG, KR>), dim3(cg.Vc * a.nsplit, ceil_div(nrhs, RG)), dim3(256), 0, st, V, x,
                          partial, a, nrhs);
   } else if (nrhs >= 2 && cg.Nv <= 32 && (f64 || g.Ls % 2 == 0)) {
-    const int nt = std::min(4, ceil_div(nrhs, 8));
+    const int nt = std::max(column_tiles, std::min(4, ceil_div(nrhs, 8)));
     a.nsplit = restrict_splits(cg.Vc);
     const dim3 grid(cg.Vc * a.nsplit, ceil_div(nrhs, 8 * nt));
     const bool wide = g.Ls % (f64 ? 2 : 4) == 0;  // 32 bytes per lane: a group of four lanes reads whole 128-byte lines
@@ -917,9 +917,9 @@ void prolong_op(const C2* V, const CC2* coarse, C2* fine, bool accumulate, const
 }
 
 template void restrict_op<double2, double2>(const double2*, const double2*, double2*, double*,
-                                            const Geometry&, const CoarseGeometry&, int, hipStream_t, bool);
+                                            const Geometry&, const CoarseGeometry&, int, hipStream_t, bool, int);
 template void restrict_op<float2, float2>(const float2*, const float2*, float2*, double*, const Geometry&,
-                                          const CoarseGeometry&, int, hipStream_t, bool);
+                                          const CoarseGeometry&, int, hipStream_t, bool, int);
 template void prolong_op<double2, double2>(const double2*, const double2*, double2*, bool, const Geometry&,
                                            const CoarseGeometry&, int, hipStream_t);
 template void prolong_op<float2, float2>(const float2*, const float2*, float2*, bool, const Geometry&,
@@ -942,7 +942,7 @@ bool orthonormalise_basis(double2* V, const Geometry& g, const CoarseGeometry& c
                          G.as<double2>(), a);
       MG_LAUNCH_CHECK();
     } else {
-      restrict_op<double2, double2>(V, V, G.as<double2>(), part.as<double>(), g, cg, cg.Nv, st, false);  // Gram matrices
+      restrict_op<double2, double2>(V, V, G.as<double2>(), part.as<double>(), g, cg, cg.Nv, st, false, 1);  // Gram matrices
     }
     hipLaunchKernelGGL(k_chol_inv, dim3(npanel), dim3(64), 0, st, G.as<double2>(), W.as<double2>(), stat.as<int>(),
                        cg.Vc, cg.Nv);

@@ -75,18 +75,20 @@ bool dslash_ftile_desc(const Geometry& g, int i, int nrhs, int desc[4], int* fla
 
 // transfer.hip
 size_t restrict_partial_doubles(const CoarseGeometry& cg, int nrhs);
+// column_tiles: at least so many tiles of eight right-hand sides per launch (the number
+// decides how often FP64 sums are compensated, so a result that may not depend on
+// the batch fixes it)
 template <class C2, class CC2>
 void restrict_op(const C2* V, const C2* x, CC2* coarse, double* partial, const Geometry& g,
-                 const CoarseGeometry& cg, int nrhs, hipStream_t st, bool keep_order = false);
+                 const CoarseGeometry& cg, int nrhs, hipStream_t st, bool keep_order = false, int column_tiles = 1);
 template <class C2, class CC2>
 void prolong_op(const C2* V, const CC2* coarse, C2* fine, bool accumulate, const Geometry& g,
                 const CoarseGeometry& cg, int nrhs, hipStream_t st);
 bool orthonormalise_basis(double2* V, const Geometry& g, const CoarseGeometry& cg, bool keep_order, hipStream_t st);
 
 // coarse.hip
-int coarse_build_columns(const Geometry& g);  // columns built together (sizes the builds' workspaces)
 void build_coarse_op(const double2* Vhat, const double2* gauge, double2* Dc, double2* work9, double2* cwork,
-                     double* partial, const Geometry& g, const CoarseGeometry& cg, double M5, double mf,
+                     double* partial, const Geometry& g, const CoarseGeometry& cg, double M5, double mf, int columns,
                      hipStream_t st);
 void finish_coarse_op(CoarseStore& Dc, CoarseStore& DcH, const CoarseGeometry& cg, hipStream_t st);
 void coarse_apply64(const CoarseStore& s, const double2* x, double2* y, const CoarseGeometry& cg, int nrhs,

@@ -69,3 +69,11 @@ def test_row_split_rounds(tmp_path):
         assert split or rounds > 1, (v, mt, f64, cg)
     # 162 sites x 64 dof, one right-hand side: 73 us split, 61 with whole sites
     assert evaluate(tmp_path, "sq_split_rows(q[0], (int)q[1], q[2], q[3])", [(162, 4, 1, 0), (162, 4, 0, 0)]) == [0, 0]
+
+
+def test_coarse_build_memory(tmp_path):
+    """Three columns at a time only where their fields leave half of the free memory."""
+    field = 12 * 16 * 16 * 4096 * 32  # bytes of an FP64 field on 16^3x32x16
+    calls = [(field, free) for free in (0, 9 * field, 27 * field, 53 * field, 54 * field, 10**12)]
+    calls += [(16 * 10**9 // 27, 10**12), (16 * 10**9 // 27 + 1, 10**12)]
+    assert evaluate(tmp_path, "coarse_build_columns((double)q[0], (double)q[1])", calls) == [1, 1, 1, 1, 3, 3, 3, 1]

@@ -67,8 +67,27 @@ def dslash_kernel_name(flags):
     return "k_dslash_tq (t-march)" if not flags & 1 else "k_dslash_tp (t-march, reloads)"
 
 
+START = time.perf_counter()
+
+
 def log(msg):
-    print(msg, file=sys.stderr, flush=True)
+    print(f"[{time.perf_counter() - START:6.1f} s] {msg}", file=sys.stderr, flush=True)
+
+
+class Budget:
+    """Which side legs still fit: one is left out when its usual length would pass the
+    limit in seconds since the start, so that the line with the timed result comes
+    out within it however many steps were asked for.  A limit of 0 fits all."""
+
+    def __init__(self, limit, clock=lambda: time.perf_counter() - START):
+        self.limit, self.clock, self.skipped = limit, clock, []
+
+    def fits(self, name, seconds):
+        if self.limit <= 0 or self.clock() + seconds <= self.limit:
+            return True
+        self.skipped.append(name)
+        log(f"{name} left out: about {seconds} s would pass the budget of {self.limit} s")
+        return False
 
 
 def mem(tag):
@@ -377,14 +396,15 @@ def mass_leg(mg, U_dev, B_main, log):
 
     out = []
     U06 = None
+    W9 = torch.from_numpy(random_starts(L_MAIN, LS, NVEC // 2, 21)).cuda()
+    Wsq = torch.from_numpy(random_starts(L_MAIN, LS, SQ_NVEC, 21)).cuda()
     for eps in (0.3, 0.6):
         if eps == 0.6:
             U06 = torch.from_numpy(prepare_gauge(L_MAIN, 0.6, 13, ape_steps=2)).cuda()
         for mf in (0.01, 0.003, 0.001):
             h = mg.Handle(L_MAIN, LS, M5, mf)
             mg.mgdwf_set_gauge(h, U_dev if eps == 0.3 else U06)
-            srep = mg.mgdwf_setup(h, mg_params(mg, "f64", "f64"),
-                                  torch.from_numpy(random_starts(L_MAIN, LS, NVEC // 2, 21)).cuda())
+            srep = mg.mgdwf_setup(h, mg_params(mg, "f64", "f64"), W9)
             mg.mgdwf_set_mg_params(h, mg_params(mg, "f32", "f16"))
             b = B_main[0].contiguous()
             x = torch.zeros_like(b)
@@ -406,8 +426,7 @@ def mass_leg(mg, U_dev, B_main, log):
             h.close()
             h = mg.Handle(L_MAIN, LS, M5, mf)
             mg.mgdwf_set_gauge(h, U_dev if eps == 0.3 else U06)
-            mg.mgdwf_setup(h, sq_params(mg, "f64", "f64"),
-                           torch.from_numpy(random_starts(L_MAIN, LS, SQ_NVEC, 21)).cuda())
+            mg.mgdwf_setup(h, sq_params(mg, "f64", "f64"), Wsq)
             mg.mgdwf_set_mg_params(h, sq_params(mg, "f32", "f32"))
             x.zero_()
             torch.cuda.synchronize()
@@ -657,6 +676,8 @@ def main():
     ap.add_argument("--no-squared", action="store_true", help="skip the squared-operator multigrid step")
     ap.add_argument("--no-low-modes", action="store_true", help="skip the low-mode coverage on the 4^4 lattice")
     ap.add_argument("--no-u1", action="store_true", help="skip the 2D U(1) test problem")
+    ap.add_argument("--budget", type=float, default=540.0,
+                    help="seconds since the start that the legs after the timed steps may reach (0: no limit)")
     args = ap.parse_args()
     if args.gpus != 1 or int(os.environ.get("WORLD_SIZE", "1")) > 1:
         print("bench.py runs on one GPU only: the library has no multi-GPU path (use --gpus 1)", file=sys.stderr)
@@ -864,35 +885,37 @@ def main():
                      "achieved": gbs32_12, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs32_12 / HBM_PEAK_GBS,
                      "algorithmic_bytes": bytes32_12, "launch_us": ms32_12 * 1e3, "traffic": counted_traffic(tiling["id"])},
     }
+    budget = Budget(args.budget)
+    if not args.no_cpu_baseline and budget.fits("cpu_baseline", 10):
+        log("cpu baseline (oracle) ...")
+        out["cpu_baseline"] = cpu_baseline(counts, x_check, b_check)
+        log(f"oracle check of the GPU solution: {out['cpu_baseline']['oracle_check']}")
     # the legs below change the main handle's setup, so they come last
-    if not args.no_squared:
+    if not args.no_squared and budget.fits("squared_operator_mg", 50):
         mg.mgdwf_trim(h)
         torch.cuda.empty_cache()
         out["squared_operator_mg"] = squared_leg(mg, U_dev, B, log)
-    if not args.no_low_modes:
+    if not args.no_low_modes and budget.fits("low_mode_coverage", 20):
         out["low_mode_coverage"] = low_modes_leg(mg, log)
-    if not args.no_u1:
+    if not args.no_u1 and budget.fits("u1_2d", 1):
         out["u1_2d"] = u1_2d_leg(mg, log)
-    if not args.no_mass_scan:
+    if not args.no_mass_scan and budget.fits("mass_scan", 150):
         mg.mgdwf_trim(h)
         torch.cuda.empty_cache()
         out["mass_scan"] = mass_leg(mg, U_dev, B, log)
-    if not args.no_ragged:
+    if not args.no_ragged and budget.fits("ragged_batch", 25):
         try:
             out["ragged_batch"] = ragged_leg(mg, h, B, log)
         except (mg.MgdwfError, AssertionError) as e:
             mem("ragged leg failed")
             out["ragged_batch"] = {"error": str(e)}
-    if not args.no_learned:
+    if not args.no_learned and budget.fits("learned_setup", 165):
         try:
             out["learned_setup"] = learned_leg(mg, h, fields_future, c5_future, log)
         except (mg.MgdwfError, AssertionError) as e:
             mem("learned leg failed")
             out["learned_setup"] = {"error": str(e)}
-    if not args.no_cpu_baseline:
-        log("cpu baseline (oracle) ...")
-        out["cpu_baseline"] = cpu_baseline(counts, x_check, b_check)
-        log(f"oracle check of the GPU solution: {out['cpu_baseline']['oracle_check']}")
+    out["legs_left_out"] = budget.skipped
     h.close()
     print(json.dumps(out), flush=True)
 

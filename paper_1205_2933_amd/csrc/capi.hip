@@ -364,10 +364,11 @@ mgdwf_status mgdwf_apply_dwf(mgdwf_handle h, const double* in, double* out, int3
     const long long n = h->fine_len() * nrhs;
     // One launch on the canonical fields where that is faster than packing, the
     // internal-layout kernel and unpacking: in FP64 everywhere (16^3x32x16, 12
-    // fields: 4.4 against 7.1 ms; 4^4x8: 5.0 against 12 us); in FP32, whose
-    // internal-layout kernels are the tiled ones, on small fields (4^4x8: 4.9
-    // against 15.3 us; 9x7x5x11x5, 3 fields: 16.2 against 21.5; 8^3x16x16, one
-    // field of 1.6e6 numbers: 30.5 against 28.4), unless a tiling was chosen
+    // fields: 4.3 against 7.1 ms; 4^4x8: 5.1 against 10 us); in FP32, whose
+    // internal-layout kernels are the tiled ones, on small fields (4^4x8: 5.2
+    // against 15.4 us; 9x7x5x11x5, 3 fields: 18.9 against 21.4; 8^4x16: 20.6 against
+    // 25.0; 8^3x16x16, one field of 1.6e6 numbers: 38.8 against 28.5), unless a
+    // tiling was chosen
     if (h->model == 0 && prec == MGDWF_F64) {
       dslash_canonical<double2>(x, y, h->U64.as<double2>(), h->g, h->M5, h->mf, dagger != 0, nrhs, h->st);
     } else if (h->model == 0 && h->g.ftile < 0 && n <= kCanonicalF32) {

@@ -35,7 +35,8 @@ inline int restrict_splits_general(int Vc, int rows, int nrhs, bool f64) {
 // 64 dof there do not (one right-hand side: 194 against 184).
 inline int sq_ordered_group(long long Vc, int n2, int nrhs) {
   const long long fewest = (nrhs + 3) / 4, rounds = (Vc * fewest + 255) / 256;
-  if (nrhs > 4 && !(n2 == 16 && Vc >= 1024) && (Vc > (Vc % 8 != 0 ? 128 : 160) || rounds >= 3 * ((nrhs + 15) / 16))) return 0;
+  const bool many = Vc > (Vc % 8 != 0 ? 128 : 160) || rounds >= 3 * ((nrhs + 15) / 16);
+  if (nrhs > 4 && many && !(n2 == 16 && Vc >= 1024)) return 0;
   if (nrhs == 1 && n2 == 64 && Vc >= 1024) return 0;
   const long long groups = std::max(fewest, 256 * rounds / Vc), least = Vc > 32 && Vc % 8 != 0 ? 2 : 1;
   return (int)std::min<long long>(nrhs, std::max(least, (nrhs + groups - 1) / groups));

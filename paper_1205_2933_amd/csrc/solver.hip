@@ -904,8 +904,10 @@ void mg_setup(mgdwf_ctx* c, const mgdwf_mg_params& p, double2* W, mgdwf_setup_re
   int nsw = 0;
   // The vectors are independent: their CG runs and sweeps take them in
   // groups, so the workspaces (six fields per vector for CG, about forty for
-  // a V-cycle-preconditioned sweep) stay bounded on large lattices; every
-  // per-vector sum is the same as in one batch.
+  // a V-cycle-preconditioned sweep) stay bounded on large lattices.  A 9-point
+  // setup's shorter last group may take other FP64 kernels (the tile Dslash and the
+  // MFMA restriction depend on the number of fields), so its sums may differ in rounding
+  // from those of one batch.
   const double field_bytes = (double)nf * sizeof(double2);
   const int g0 = std::max(1, std::min(nh, std::min(4, (int)(48e9 / (6.0 * field_bytes)))));
   for (int k0 = 0; k0 < nh; k0 += g0)

@@ -140,10 +140,10 @@ __global__ __launch_bounds__(256) void k_restrict(const C2* __restrict__ V, cons
 // case) and the sums are exact to the inputs' rounding (4.4e-8 against 64 bits,
 // 8.6e-8 to 2.0e-7 in the VALU form).  FP64 rows are added with a compensated sum
 // every 8 products (every 8 U with four column tiles or more than four tiles, whose
-// registers allow one wavefront per SIMD): 1.5e-16 to 1.8e-16
-// against 80 bits, where plain chains over a row group had 2.7e-16 to 3.9e-16 at the
-// same time and the VALU form has 1.7e-16 to 2.5e-16; its serial Gram pass leaves a
-// basis 1.1e-15 to 4.6e-15 from orthonormal, this one 2e-16.  Bound by HBM at few
+// registers allow one wavefront per SIMD): 1.5e-16 to 1.8e-16 against 80 bits, where
+// plain chains over a row group had 2.7e-16 to 3.9e-16 in the same time and the VALU
+// form has 1.7e-16 to 2.5e-16; its serial Gram pass leaves a basis 1.1e-15 to 4.6e-15
+// from orthonormal, this one 2e-16.  Bound by HBM (3.8 TB/s, read once) at few
 // right-hand sides, by the FP64 matrix rate at many.  Against the VALU forms, 24
 // columns: 12 FP32 right-hand sides on 16^3x32x16 3.12 -> 1.97 ms, on 8^3x16x16 365 ->
 // 130 us; FP64 on 8^3x16x16, nine 1071 us -> 27 in 362 us, four 430 -> 192 us.
@@ -151,8 +151,9 @@ __global__ __launch_bounds__(256) void k_restrict(const C2* __restrict__ V, cons
 typedef double rd4 __attribute__((ext_vector_type(4)));
 
 template <class C2, int KT, int NT, int U>
-__global__ __launch_bounds__(256, sizeof(C2) == 16 && KT == 2 && NT <= 2 ? 2 : 1) void k_restrict_mfma(const C2* __restrict__ V, const C2* __restrict__ x,
-                                                       double* __restrict__ partial, BlockArgs a, int nrhs) {
+__global__ __launch_bounds__(256, sizeof(C2) == 16 && KT == 2 && NT <= 2 ? 2 : 1)
+void k_restrict_mfma(const C2* __restrict__ V, const C2* __restrict__ x, double* __restrict__ partial, BlockArgs a,
+                     int nrhs) {
   using T = typename real_of<C2>::type;
   constexpr bool F64 = sizeof(T) == 8;
   constexpr int W1 = F64 ? 1 : 2;  // consecutive s in 16 bytes

@@ -38,7 +38,6 @@ __global__ __launch_bounds__(BS) void k_finalize_rhs(const double* __restrict__ 
   if (threadIdx.x == 0) sl[rhs * NSLOT + dst + comp] = acc;
 }
 
-// x (+)= alpha p;  r -= alpha q;  alpha = sl[num] / sl[den] (real);  partial |r|^2.
 // Slot `s`, or with np > 0 the sum that finalize_rhs would put there (its order),
 // added from the np partials by every workgroup: one launch less where they are few.
 __device__ __forceinline__ double slot_or_sum(const double* sl, int rhs, int s, const double* part, int np, int ncomp) {
@@ -52,6 +51,7 @@ __device__ __forceinline__ double slot_or_sum(const double* sl, int rhs, int s, 
   return tot;
 }
 
+// x (+)= alpha p;  r -= alpha q;  alpha = sl[num] / sl[den] (real);  partial |r|^2.
 template <class C2>
 __global__ __launch_bounds__(256) void k_mr_update(C2* __restrict__ x, C2* __restrict__ r, const C2* __restrict__ p,
                                                    const C2* __restrict__ q, long long n, const double* __restrict__ sl,
